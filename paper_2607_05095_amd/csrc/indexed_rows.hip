@@ -4,11 +4,11 @@
 //
 // fast_occurrence_csr: for every row, its positions in ascending order -- a
 // stable counting sort of the index, done as an LSD radix sort of (key,
-// position) pairs over 8-bit digits.  Each pass: per-tile digit histograms,
-// one scan of the (digit, tile) counts, and a scatter in which every item
-// finds its rank among the tile's items with the same digit from 8 wave
-// ballots, in position order -- stable, so after the last pass each row's
-// positions are ascending.  Positions whose index is outside the row range
+// position) pairs over digits of at most 8 bits.  Each pass: per-tile digit
+// histograms, one scan of the (digit, tile) counts, and a scatter in which
+// every item finds its rank among the tile's items with the same digit from
+// wave ballots, in position order -- stable, so after the last pass each
+// row's positions are ascending.  Positions whose index is outside the row range
 // get the key num_rows and sort behind every valid one.
 //
 // fast_index_add_rows: dst[u] = sum of src rows over the occurrences of u,
@@ -25,32 +25,24 @@
 namespace fast {
 
 // ------------------------------------------------------------------ radix sort
-constexpr int RS_THREADS = 256;
+// A pass is bound by its scattered writes and by launch latency, not by its
+// bytes (8 read and 8 written per item): a tile is sorted by digit in LDS
+// first, so that the items of one digit leave as one contiguous run, and the
+// digits are as narrow as the pass count allows (7 + 6 + 6 bits for 19-bit
+// keys), so that a run of a tile is 32-64 items.  Items are loaded once and
+// keep their rank in registers; the counts' prefixes take one launch, a
+// workgroup per digit.  Against tiles of 2048 items scattered straight from
+// registers with 8-bit digits and a two-launch scan, one list of 2.64 M Zipf
+// positions over 4e5 rows went from 174 to 85 us (first scatter 56 -> 15),
+// of 1.32 M uniform positions over 1.2e6 rows from 133 to 66 us.
+constexpr int RS_THREADS = 512;
 constexpr int RS_WAVES = RS_THREADS / 64;
 constexpr int RS_ROUNDS = 8;                        // 64-item rounds per wave
-constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;     // 2048 items per tile
-constexpr int RS_DIGITS = 256;
+constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;     // 4096 items per tile
+constexpr int RS_MAX_BITS = 8;
+constexpr int RS_DIGITS = 1 << RS_MAX_BITS;
 
 inline int64_t rs_tiles(int64_t n) { return (n + RS_TILE - 1) / RS_TILE; }
-
-// Key and value of item i: in the first pass the key comes from the index
-// (num_rows for a position outside the row range) and the value is i.
-struct RsSrc {
-  const int32_t* index;   // first pass
-  const int32_t* keys;    // later passes
-  const int32_t* vals;
-  int32_t num_rows;
-  __device__ void get(int64_t i, uint32_t& k, int32_t& v) const {
-    if (index) {
-      const int32_t x = index[i];
-      k = (x >= 0 && x < num_rows) ? uint32_t(x) : uint32_t(num_rows);
-      v = int32_t(i);
-    } else {
-      k = uint32_t(keys[i]);
-      v = vals[i];
-    }
-  }
-};
 
 // Items of a tile: wave w takes items [w*512, (w+1)*512) in rounds of 64
 // consecutive items, so (wave, round, lane) order is position order.
@@ -58,11 +50,41 @@ __device__ __forceinline__ int64_t rs_item(int64_t tile, int w, int r, int lane)
   return tile * RS_TILE + int64_t(w) * (RS_ROUNDS * 64) + r * 64 + lane;
 }
 
+// Keys and values of a thread's items: in the first pass the key comes from
+// the index (num_rows for a position outside the row range) and the value is
+// the position.  Positions past n read the last item; the caller masks them.
+struct RsSrc {
+  const int32_t* index;   // first pass
+  const int32_t* keys;    // later passes
+  const int32_t* vals;
+  int32_t num_rows;
+  __device__ void load_keys(int64_t tile, int w, int lane, int64_t n, uint32_t (&k)[RS_ROUNDS]) const {
+    const int32_t* __restrict__ p = index ? index : keys;
+#pragma unroll
+    for (int r = 0; r < RS_ROUNDS; ++r) {
+      const int64_t i = rs_item(tile, w, r, lane);
+      k[r] = uint32_t(p[i < n ? i : n - 1]);
+    }
+    if (index) {
+#pragma unroll
+      for (int r = 0; r < RS_ROUNDS; ++r) k[r] = k[r] < uint32_t(num_rows) ? k[r] : uint32_t(num_rows);
+    }
+  }
+  __device__ void load_vals(int64_t tile, int w, int lane, int64_t n, int32_t (&v)[RS_ROUNDS]) const {
+#pragma unroll
+    for (int r = 0; r < RS_ROUNDS; ++r) {
+      const int64_t i = rs_item(tile, w, r, lane);
+      v[r] = index ? int32_t(i) : vals[i < n ? i : n - 1];
+    }
+  }
+};
+
 // Lanes of the wave holding the same digit as this lane (inactive lanes excluded).
+template <int BITS>
 __device__ __forceinline__ uint64_t digit_match(uint32_t d, bool valid) {
   uint64_t m = __ballot(valid);
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
+  for (int b = 0; b < BITS; ++b) {
     const bool bit = (d >> b) & 1u;
     const uint64_t bal = __ballot(bit);
     m &= bit ? bal : ~bal;
@@ -70,106 +92,240 @@ __device__ __forceinline__ uint64_t digit_match(uint32_t d, bool valid) {
   return m;
 }
 
-// hist[d * T + tile] = items of the tile whose digit is d.
+// hist[d * T + tile] = items of the tile whose digit is d.  The lanes that
+// share the first lane's digit add up to one LDS atomic: after a first pass
+// a hub row's items lie side by side, and 64 atomics on one digit serialise.
+template <int BITS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_hist(RsSrc src, int64_t n, int shift,
                                                        uint32_t* hist, int64_t T) {
-  __shared__ uint32_t s_h[RS_DIGITS];
-  s_h[threadIdx.x] = 0;
-  __syncthreads();
+  constexpr int BINS = 1 << BITS;
+  __shared__ uint32_t s_h[BINS];
+  if (threadIdx.x < BINS) s_h[threadIdx.x] = 0;
   const int64_t tile = blockIdx.x;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  uint32_t key[RS_ROUNDS];
+  src.load_keys(tile, w, lane, n, key);
+  __syncthreads();
 #pragma unroll
-  for (int k = 0; k < RS_ROUNDS; ++k) {
-    const int64_t i = tile * RS_TILE + int64_t(k) * RS_THREADS + threadIdx.x;
-    if (i < n) {
-      uint32_t key;
-      int32_t v;
-      src.get(i, key, v);
-      atomicAdd(&s_h[(key >> shift) & 255u], 1u);
-    }
+  for (int r = 0; r < RS_ROUNDS; ++r) {
+    const bool valid = rs_item(tile, w, r, lane) < n;     // a prefix of the lanes
+    const uint32_t d = (key[r] >> shift) & (BINS - 1);
+    const uint32_t d0 = uint32_t(__builtin_amdgcn_readfirstlane(int(d)));
+    const uint64_t same = __ballot(valid && d == d0);
+    if (lane == 0 && same) atomicAdd(&s_h[d0], uint32_t(__popcll(same)));
+    else if (valid && d != d0) atomicAdd(&s_h[d], 1u);
   }
   __syncthreads();
-  hist[int64_t(threadIdx.x) * T + tile] = s_h[threadIdx.x];
+  if (threadIdx.x < BINS) hist[int64_t(threadIdx.x) * T + tile] = s_h[threadIdx.x];
 }
 
-// base[d * T + tile] (after the scan) = first output slot of the tile's
-// items with digit d.  Writes keys (unless NULL) and values.
+// One workgroup per digit d: hist[d * T ...] becomes its exclusive prefix
+// over the tiles, total[d] the digit's count.
+constexpr int RS_ROW_ITEMS = 4;
+__global__ void __launch_bounds__(SCAN_THREADS) k_rs_rowscan(uint32_t* hist, int64_t T, uint32_t* total) {
+  __shared__ uint32_t lds4[4];
+  uint32_t* row = hist + int64_t(blockIdx.x) * T;
+  uint32_t carry = 0;
+  for (int64_t t0 = 0; t0 < T; t0 += SCAN_THREADS * RS_ROW_ITEMS) {
+    const int64_t i0 = t0 + int64_t(threadIdx.x) * RS_ROW_ITEMS;
+    uint32_t c[RS_ROW_ITEMS], sum = 0;
+#pragma unroll
+    for (int k = 0; k < RS_ROW_ITEMS; ++k) {
+      c[k] = i0 + k < T ? row[i0 + k] : 0u;
+      sum += c[k];
+    }
+    uint32_t tot;
+    uint32_t run = carry + block_exclusive_scan(sum, lds4, tot);
+#pragma unroll
+    for (int k = 0; k < RS_ROW_ITEMS; ++k) {
+      if (i0 + k < T) row[i0 + k] = run;
+      run += c[k];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// Exclusive prefixes of x and of y over the workgroup's RS_THREADS threads.
+__device__ __forceinline__ void rs_block_scan2(uint32_t& x, uint32_t& y, uint2* lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t ix = x, iy = y;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t ux = __shfl_up(ix, o, 64), uy = __shfl_up(iy, o, 64);
+    if (lane >= o) {
+      ix += ux;
+      iy += uy;
+    }
+  }
+  if (lane == 63) lds[w] = make_uint2(ix, iy);
+  __syncthreads();
+  uint32_t bx = 0, by = 0;
+#pragma unroll
+  for (int j = 0; j < RS_WAVES; ++j) {
+    bx += j < w ? lds[j].x : 0u;
+    by += j < w ? lds[j].y : 0u;
+  }
+  x = bx + ix - x;
+  y = by + iy - y;
+}
+
+// base[d * T + tile]: items of digit d in the tiles before this one; total[d]:
+// items of digit d.  The tile is sorted by digit in LDS (stable: wave, round,
+// lane order), then written out run by run.
+template <int BITS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(RsSrc src, int64_t n, int shift,
-                                                          const uint32_t* base, int64_t T,
-                                                          int32_t* keys_out, int32_t* vals_out) {
-  __shared__ uint32_t s_cnt[RS_WAVES][RS_DIGITS];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+                                                          const uint32_t* __restrict__ base,
+                                                          const uint32_t* __restrict__ total,
+                                                          int64_t T, int32_t* __restrict__ keys_out,
+                                                          int32_t* __restrict__ vals_out) {
+  constexpr int BINS = 1 << BITS;
+  static_assert(BINS <= RS_THREADS, "a thread per digit");
+  __shared__ uint32_t s_cnt[RS_WAVES][BINS];
+  __shared__ uint2 s_scan[RS_WAVES];
+  __shared__ uint32_t s_base[BINS];
+  __shared__ int32_t s_key[RS_TILE], s_val[RS_TILE];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, b = threadIdx.x;
   const int64_t tile = blockIdx.x;
   const uint64_t lt = (uint64_t(1) << lane) - 1;
-#pragma unroll
-  for (int j = 0; j < RS_WAVES; ++j) s_cnt[j][threadIdx.x] = 0;
+  uint32_t key[RS_ROUNDS], rank[RS_ROUNDS];
+  int32_t val[RS_ROUNDS];
+  src.load_keys(tile, w, lane, n, key);
+  src.load_vals(tile, w, lane, n, val);
+  const uint32_t before = b < BINS ? base[int64_t(b) * T + tile] : 0u;
+  uint32_t dbase = b < BINS ? total[b] : 0u;
+  for (int j = b; j < RS_WAVES * BINS; j += RS_THREADS) (&s_cnt[0][0])[j] = 0u;
   __syncthreads();
-  // A: counts per (wave, digit)
+  // rank of each item among the wave's items of its digit
+#pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) {
-    const int64_t i = rs_item(tile, w, r, lane);
-    const bool valid = i < n;
-    uint32_t key = 0;
-    int32_t v = 0;
-    if (valid) src.get(i, key, v);
-    const uint32_t d = (key >> shift) & 255u;
-    const uint64_t m = digit_match(d, valid);
-    if (valid && (m & lt) == 0) s_cnt[w][d] += uint32_t(__popcll(m));   // lowest lane of its digit
+    const bool valid = rs_item(tile, w, r, lane) < n;
+    const uint32_t d = (key[r] >> shift) & (BINS - 1);
+    const uint64_t m = digit_match<BITS>(d, valid);
+    const uint32_t seen = s_cnt[w][d];
+    rank[r] = seen + uint32_t(__popcll(m & lt));
+    if (valid && (m & lt) == 0) s_cnt[w][d] = seen + uint32_t(__popcll(m));   // lowest lane of its digit
   }
   __syncthreads();
-  // exclusive prefix over the waves, per digit
-  {
-    uint32_t run = 0;
+  // prefix over the waves, then over the digits: s_cnt[w][d] becomes the
+  // tile position of wave w's first item of digit d
+  uint32_t c[RS_WAVES], start = 0;
+  if (b < BINS) {
 #pragma unroll
     for (int j = 0; j < RS_WAVES; ++j) {
-      const uint32_t c = s_cnt[j][threadIdx.x];
-      s_cnt[j][threadIdx.x] = run;
-      run += c;
+      c[j] = start;
+      start += s_cnt[j][b];
+    }
+  }
+  rs_block_scan2(start, dbase, s_scan);
+  if (b < BINS) {
+#pragma unroll
+    for (int j = 0; j < RS_WAVES; ++j) s_cnt[j][b] = start + c[j];
+    s_base[b] = dbase + before - start;        // output slot of tile position p: s_base[d] + p
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RS_ROUNDS; ++r) {
+    if (rs_item(tile, w, r, lane) < n) {
+      const uint32_t p = s_cnt[w][(key[r] >> shift) & (BINS - 1)] + rank[r];
+      s_key[p] = int32_t(key[r]);
+      s_val[p] = val[r];
     }
   }
   __syncthreads();
-  // B: rank inside the tile and scatter
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    const int64_t i = rs_item(tile, w, r, lane);
-    const bool valid = i < n;
-    uint32_t key = 0;
-    int32_t v = 0;
-    if (valid) src.get(i, key, v);
-    const uint32_t d = (key >> shift) & 255u;
-    const uint64_t m = digit_match(d, valid);
-    const uint32_t before = s_cnt[w][d];
-    if (valid) {
-      const int64_t pos = int64_t(base[int64_t(d) * T + tile]) + before + uint32_t(__popcll(m & lt));
-      if (keys_out) keys_out[pos] = int32_t(key);
-      vals_out[pos] = v;
-    }
-    if (valid && (m & lt) == 0) s_cnt[w][d] = before + uint32_t(__popcll(m));
+  const int64_t left = n - tile * RS_TILE;
+  const int m = int(left < RS_TILE ? left : RS_TILE);
+  for (int p = b; p < m; p += RS_THREADS) {
+    const uint32_t k = uint32_t(s_key[p]);
+    const uint32_t pos = s_base[(k >> shift) & (BINS - 1)] + uint32_t(p);
+    keys_out[pos] = int32_t(k);
+    vals_out[pos] = s_val[p];
   }
 }
 
-struct InU32 {
-  const uint32_t* p;
-  __device__ uint32_t operator()(int64_t i) const { return p[i]; }
-};
-struct OutU32InPlace {
-  uint32_t* p;
-  __device__ void operator()(int64_t i, uint32_t prefix, uint32_t) const { p[i] = prefix; }
-};
+template <int BITS>
+static void rs_pass(const RsSrc& src, int64_t n, int shift, uint32_t* hist, uint32_t* total,
+                    int32_t* keys_out, int32_t* vals_out, hipStream_t st) {
+  const int64_t T = rs_tiles(n);
+  hipLaunchKernelGGL(k_rs_hist<BITS>, dim3(uint32_t(T)), dim3(RS_THREADS), 0, st, src, n, shift, hist, T);
+  hipLaunchKernelGGL(k_rs_rowscan, dim3(1u << BITS), dim3(SCAN_THREADS), 0, st, hist, T, total);
+  hipLaunchKernelGGL(k_rs_scatter<BITS>, dim3(uint32_t(T)), dim3(RS_THREADS), 0, st, src, n, shift,
+                     hist, total, T, keys_out, vals_out);
+}
 
 // occ_off[u] = number of sorted keys below u (a lower bound in the sorted
 // keys; positions outside the row range carry the key num_rows), u in
 // [0, num_rows].  No atomics: a hub row's count costs nothing extra.
-__global__ void __launch_bounds__(RS_THREADS) k_occ_offsets(const int32_t* __restrict__ keys,
-                                                           int64_t n, int64_t num_rows,
-                                                           int32_t* __restrict__ occ_off) {
-  const int64_t u = int64_t(blockIdx.x) * RS_THREADS + threadIdx.x;
-  if (u > num_rows) return;
-  int64_t lo = 0, hi = n;
+// A workgroup takes OO_ROWS consecutive rows: two of its waves find where its
+// rows' keys begin and end, 64 probes at a time, and every row is then searched
+// for in that range alone -- in LDS when it is short, as it is but for hub
+// rows.  (A search over all n keys per row is bound by its probes: 22 us for
+// 1.25 M rows, 12 this way; 0.41 M rows with a hub 9.6 and 11.5.)
+constexpr int OO_THREADS = 256;
+constexpr int OO_PER = 2;
+constexpr int OO_ROWS = OO_PER * OO_THREADS;
+constexpr int OO_KEYS = 4096;
+
+// First position in [0, n) whose key is not below u, n if there is none;
+// every lane of the wave takes part and returns it.
+__device__ __forceinline__ int64_t wave_lower_bound(const int32_t* __restrict__ keys, int64_t n,
+                                                    int64_t u) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = n;                      // keys before lo are below u, keys from hi on are not
   while (lo < hi) {
-    const int64_t mid = lo + ((hi - lo) >> 1);
-    if (int64_t(keys[mid]) < u) lo = mid + 1; else hi = mid;
+    const int64_t step = (hi - lo + 63) >> 6;  // probes lo + step - 1, lo + 2 step - 1, ...
+    const int64_t p = lo + int64_t(lane + 1) * step - 1;
+    const bool below = p < hi && int64_t(keys[p]) < u;
+    const int c = __popcll(__ballot(below));   // the probes below u come first
+    const int64_t cap = lo + int64_t(c + 1) * step - 1;
+    lo += int64_t(c) * step;
+    hi = cap < hi ? cap : hi;
   }
-  occ_off[u] = int32_t(lo);
+  return lo;
 }
 
+__global__ void __launch_bounds__(OO_THREADS) k_occ_offsets(const int32_t* __restrict__ keys,
+                                                           int64_t n, int64_t num_rows,
+                                                           int32_t* __restrict__ occ_off) {
+  __shared__ int64_t s_range[2];
+  __shared__ int32_t s_key[OO_KEYS];
+  const int64_t u0 = int64_t(blockIdx.x) * OO_ROWS;
+  const int w = threadIdx.x >> 6;
+  if (w < 2) {
+    const int64_t p = wave_lower_bound(keys, n, u0 + w * OO_ROWS);
+    if ((threadIdx.x & 63) == 0) s_range[w] = p;
+  }
+  __syncthreads();
+  const int64_t a = s_range[0], b = s_range[1];
+  const bool small = b - a <= OO_KEYS;
+  if (small) {
+    for (int j = threadIdx.x; j < int(b - a); j += OO_THREADS) s_key[j] = keys[a + j];
+    __syncthreads();
+  }
+  // a thread's searches advance together: their probes are independent
+  int64_t lo[OO_PER], hi[OO_PER];
+#pragma unroll
+  for (int r = 0; r < OO_PER; ++r) {
+    lo[r] = 0;
+    hi[r] = b - a;
+  }
+  for (int64_t len = b - a; len > 0; len >>= 1) {
+#pragma unroll
+    for (int r = 0; r < OO_PER; ++r) {
+      const int64_t u = u0 + r * OO_THREADS + threadIdx.x;
+      const int64_t mid = (lo[r] + hi[r]) >> 1;
+      if (lo[r] < hi[r]) {
+        const int32_t k = small ? s_key[mid] : keys[a + mid];
+        if (int64_t(k) < u) lo[r] = mid + 1; else hi[r] = mid;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < OO_PER; ++r) {
+    const int64_t u = u0 + r * OO_THREADS + threadIdx.x;
+    if (u <= num_rows) occ_off[u] = int32_t(a + lo[r]);
+  }
+}
 
 __global__ void __launch_bounds__(RS_THREADS) k_ir_fill(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = int64_t(blockIdx.x) * RS_THREADS + threadIdx.x; i < n;
@@ -181,7 +337,7 @@ struct OccWs {
   int32_t* keys[2];
   int32_t* vals[2];
   uint32_t* hist;
-  void* scan_h;
+  uint32_t* total;
 };
 
 static size_t occ_layout(int64_t n, int64_t num_rows, char* base, OccWs* ws) {
@@ -197,14 +353,14 @@ static size_t occ_layout(int64_t n, int64_t num_rows, char* base, OccWs* ws) {
   char* v0 = take(size_t(n) * 4);
   char* v1 = take(size_t(n) * 4);
   char* h = take(size_t(T) * RS_DIGITS * 4);
-  char* sh = take(scan_workspace(T * RS_DIGITS));
+  char* tt = take(size_t(RS_DIGITS) * 4);
   if (ws) {
     ws->keys[0] = reinterpret_cast<int32_t*>(k0);
     ws->keys[1] = reinterpret_cast<int32_t*>(k1);
     ws->vals[0] = reinterpret_cast<int32_t*>(v0);
     ws->vals[1] = reinterpret_cast<int32_t*>(v1);
     ws->hist = reinterpret_cast<uint32_t*>(h);
-    ws->scan_h = sh;
+    ws->total = reinterpret_cast<uint32_t*>(tt);
   }
   return off;
 }
@@ -611,26 +767,29 @@ extern "C" fast_status_t fast_occurrence_csr(const int32_t* index, int64_t n, in
                        st, occ_off, num_rows + 1, 0);
     return check_launch(fn);
   }
-  // positions sorted stably by key, 8 bits per pass (keys <= num_rows)
+  // positions sorted stably by key (keys <= num_rows), the key's bits split
+  // evenly over the passes
   int bits = 1;
   while ((int64_t(1) << bits) <= num_rows) ++bits;
-  const int passes = (bits + 7) / 8;
-  const int64_t T = rs_tiles(n);
-  hipError_t e = hipSuccess;
+  const int passes = (bits + RS_MAX_BITS - 1) / RS_MAX_BITS;
+  int shift = 0;
   for (int p = 0; p < passes; ++p) {
-    RsSrc src{p == 0 ? index : nullptr, w.keys[(p + 1) & 1], w.vals[(p + 1) & 1], int32_t(num_rows)};
-    const bool last = p == passes - 1;
+    const RsSrc src{p == 0 ? index : nullptr, w.keys[(p + 1) & 1], w.vals[(p + 1) & 1], int32_t(num_rows)};
     int32_t* kout = w.keys[p & 1];
-    int32_t* vout = last ? occ : w.vals[p & 1];
-    hipLaunchKernelGGL(k_rs_hist, dim3(uint32_t(T)), dim3(RS_THREADS), 0, st, src, n, 8 * p, w.hist, T);
-    e = scan_launch(InU32{w.hist}, OutU32InPlace{w.hist}, T * RS_DIGITS, w.scan_h, nullptr, nullptr, st);
-    if (e != hipSuccess) return fail(FAST_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
-    hipLaunchKernelGGL(k_rs_scatter, dim3(uint32_t(T)), dim3(RS_THREADS), 0, st, src, n, 8 * p,
-                       w.hist, T, kout, vout);
+    int32_t* vout = p == passes - 1 ? occ : w.vals[p & 1];
+    const int width = (bits - shift + passes - p - 1) / (passes - p);
+    switch (width) {
+      case 8: rs_pass<8>(src, n, shift, w.hist, w.total, kout, vout, st); break;
+      case 7: rs_pass<7>(src, n, shift, w.hist, w.total, kout, vout, st); break;
+      case 6: rs_pass<6>(src, n, shift, w.hist, w.total, kout, vout, st); break;
+      case 5: rs_pass<5>(src, n, shift, w.hist, w.total, kout, vout, st); break;
+      default: rs_pass<4>(src, n, shift, w.hist, w.total, kout, vout, st); break;   // keys of 1-4 bits
+    }
+    shift += width;
   }
   // row offsets from the sorted keys
-  hipLaunchKernelGGL(k_occ_offsets, dim3(uint32_t((num_rows + RS_THREADS) / RS_THREADS)),
-                     dim3(RS_THREADS), 0, st, w.keys[(passes - 1) & 1], n, num_rows, occ_off);
+  hipLaunchKernelGGL(k_occ_offsets, dim3(uint32_t((num_rows + OO_ROWS) / OO_ROWS)),
+                     dim3(OO_THREADS), 0, st, w.keys[(passes - 1) & 1], n, num_rows, occ_off);
   return check_launch(fn);
 }
 

@@ -71,6 +71,22 @@ def test_occurrence_csr_bit_exact(n, rows):
     assert np.array_equal(occ.cpu().numpy()[:want_off[-1]], want_occ)
 
 
+@pytest.mark.parametrize("rows", [1, 7, 15, 255, 256, 511, 32_767, 65_536, 1 << 21, (1 << 24) - 1])
+@pytest.mark.parametrize("n", [1, 63, 4095, 4096, 4097, 12_289])
+def test_occurrence_csr_digit_and_tile_edges(n, rows):
+    """Key widths around the digit splits of the sort (1 to 4 passes of 1 to 8 bits) and position
+    counts around its tiles of 4096: half of the positions in one hub row, the rest anywhere."""
+    _announce(f"occurrence csr edges n={n} rows={rows}")
+    r = np.random.default_rng(n * 31 + rows)
+    idx = r.integers(-1, rows + 1, n)
+    idx[r.random(n) < 0.5] = rows - 1
+    idx = idx.astype(np.int32)
+    off, occ = _occ_gpu(idx, rows)
+    want_off, want_occ = oracle.occurrence_csr(idx, rows)
+    assert np.array_equal(off.cpu().numpy(), want_off)
+    assert np.array_equal(occ.cpu().numpy()[:want_off[-1]], want_occ)
+
+
 @pytest.mark.parametrize("D,dt,rows", [(100, "f32", 300), (128, "bf16", 5000), (172, "f32", 40),
                                        (7, "f32", 1000), (50, "bf16", 3), (1, "f32", 100)])
 def test_index_add_rows_vs_oracle(D, dt, rows):
