@@ -253,9 +253,10 @@ static void rs_pass(const RsSrc& src, int64_t n, int shift, uint32_t* hist, uint
                      hist, total, T, keys_out, vals_out);
 }
 
-// occ_off[u] = number of sorted keys below u (a lower bound in the sorted
-// keys; positions outside the row range carry the key num_rows), u in
-// [0, num_rows].  No atomics: a hub row's count costs nothing extra.
+// Number of sorted keys below u, for u = u_first + i, i in [0, count): the
+// row offsets of the sorted positions (keys outside the row range carry the
+// key num_rows), and the segment of each edge (the offsets at or below it,
+// less one).  No atomics: a hub row's count costs nothing extra.
 // A workgroup takes OO_ROWS consecutive rows: two of its waves find where its
 // rows' keys begin and end, 64 probes at a time, and every row is then searched
 // for in that range alone -- in LDS when it is short, as it is but for hub
@@ -284,12 +285,50 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t* __restrict__ 
   return lo;
 }
 
-__global__ void __launch_bounds__(OO_THREADS) k_occ_offsets(const int32_t* __restrict__ keys,
-                                                           int64_t n, int64_t num_rows,
-                                                           int32_t* __restrict__ occ_off) {
+struct OutBound {
+  int32_t* __restrict__ out;
+  // m results from i0 on, in LDS
+  __device__ void operator()(const int32_t* below, int64_t i0, int m) const {
+    for (int j = threadIdx.x; j < m; j += OO_THREADS) out[i0 + j] = below[j];
+  }
+};
+// rec[e] = (segment of edge e, its H coefficients), 1 + H words: a sum reads
+// the two together, from one line mostly, not from two arrays (bf16 4 x 32
+// sums of 1.32 M edges into 0.74 M / 1.25 M rows: 168 -> 138 / 203 -> 183 us,
+// for 13 us more here).
+struct OutEdgeRec {
+  const float* __restrict__ scal;
+  int32_t* __restrict__ rec;
+  int H;
+  int32_t last;
+  __device__ void operator()(const int32_t* below, int64_t i0, int m) const {
+    const int w = 1 + H, de = OO_THREADS / w, dk = OO_THREADS - de * w;
+    int e = int(threadIdx.x) / w, k = int(threadIdx.x) - e * w;
+    int32_t* __restrict__ r = rec + i0 * w;
+    for (int j = threadIdx.x; j < m * w; j += OO_THREADS) {
+      if (k) {
+        r[j] = __float_as_int(scal[(i0 + e) * H + k - 1]);
+      } else {                                       // in range whatever the offsets hold
+        const int32_t v = below[e] - 1;
+        r[j] = v < 0 ? 0 : (v > last ? last : v);
+      }
+      e += de;
+      k += dk;
+      if (k >= w) {
+        k -= w;
+        ++e;
+      }
+    }
+  }
+};
+
+template <class Out>
+__global__ void __launch_bounds__(OO_THREADS) k_lower_bounds(const int32_t* __restrict__ keys,
+                                                            int64_t n, int64_t u_first,
+                                                            int64_t count, Out out) {
   __shared__ int64_t s_range[2];
-  __shared__ int32_t s_key[OO_KEYS];
-  const int64_t u0 = int64_t(blockIdx.x) * OO_ROWS;
+  __shared__ int32_t s_key[OO_KEYS], s_below[OO_ROWS];
+  const int64_t i0 = int64_t(blockIdx.x) * OO_ROWS, u0 = u_first + i0;
   const int w = threadIdx.x >> 6;
   if (w < 2) {
     const int64_t p = wave_lower_bound(keys, n, u0 + w * OO_ROWS);
@@ -321,10 +360,16 @@ __global__ void __launch_bounds__(OO_THREADS) k_occ_offsets(const int32_t* __res
     }
   }
 #pragma unroll
-  for (int r = 0; r < OO_PER; ++r) {
-    const int64_t u = u0 + r * OO_THREADS + threadIdx.x;
-    if (u <= num_rows) occ_off[u] = int32_t(a + lo[r]);
-  }
+  for (int r = 0; r < OO_PER; ++r) s_below[r * OO_THREADS + threadIdx.x] = int32_t(a + lo[r]);
+  __syncthreads();
+  out(s_below, i0, int(count - i0 < OO_ROWS ? count - i0 : OO_ROWS));
+}
+
+template <class Out>
+static void launch_lower_bounds(const int32_t* keys, int64_t n, int64_t u_first, int64_t count,
+                                const Out& out, hipStream_t st) {
+  hipLaunchKernelGGL(k_lower_bounds<Out>, dim3(uint32_t((count + OO_ROWS - 1) / OO_ROWS)),
+                     dim3(OO_THREADS), 0, st, keys, n, u_first, count, out);
 }
 
 __global__ void __launch_bounds__(RS_THREADS) k_ir_fill(int32_t* p, int64_t n, int32_t v) {
@@ -374,7 +419,9 @@ static uint32_t grid_cap(int64_t n, int64_t per, uint32_t cap = 8192) {
 // ------------------------------------------------------------------ index add
 constexpr int IA_THREADS = 256;
 constexpr int IA_PIECE = 64;   // occurrences summed by one group
-constexpr int IA_UNROLL = 4;   // rows in flight per lane
+constexpr int IA_ROWS = 4;   // rows per group of lanes on large outputs
+constexpr int64_t IA_GROUPS_FILL = 16384;   // groups that fill the chip twice
+constexpr int IA_PART_UNROLL = 4;   // partial sums in flight per lane of a long row
 
 constexpr int IA_GROUP_MIN = 16;   // fewest pieces per group of the second level
 
@@ -455,57 +502,60 @@ template <> struct VecIO<float, 8> {
   }
 };
 
-// Row sources of the index-add kernels.  Occurrence j (position p = occ[j])
-// contributes, to chunk c (VE values) of its row's sum:
+// Row sources of the index-add kernels.  Position p = occ[j] contributes, to
+// chunk c (VE values) of its row's sum:
 //   PlainRows:  src row p;
-//   ScaledRows: coefficient seg_scal[j, head] times src row occ_seg[j] --
-//               the coefficient of edge p and the destination segment it
-//               belongs to, laid out in occurrence order by k_coef_permute,
-//               one head coefficient per element (a chunk spans at most two
-//               heads, since VE <= dh).
+//   ScaledRows: coefficient scal[p, head] times src row seg[p] -- the
+//               coefficient of edge p and the destination segment it belongs
+//               to, one head coefficient per element (a chunk spans at most
+//               two heads, since VE <= dh).
 // Products are formed in fp64 (exact for fp32 factors), sums in fp64.
 template <typename T, int VE>
 struct PlainRows {
   // rows in flight per lane in the pieces of long rows, whose sums are
-  // chains of up to a thousand occurrences: 16 took the hub rows of the
-  // 1e7-node batch's layer-1 block (up to 3.1e5 occurrences) from 0.54 to
-  // 0.45 ms; the scaled source holds two coefficients more per row and
-  // stays at 4 (8 and 16 were slower there)
-  static constexpr int PIECE_UNROLL = 16;
+  // chains of up to a thousand occurrences
+  static constexpr int PIECE_UNROLL = 16, ROW_UNROLL = 8;
   const T* __restrict__ src;
   int D;
   int64_t n;
+  struct Pos {
+    int32_t p;
+  };
   struct Item {
-    float x[VE];
+    Raw<T, VE> r;
   };
   __device__ void chunk(int) {}
-  __device__ Item fetch(const int32_t* __restrict__ occ, int64_t j, int c) const {
+  __device__ Pos pos(int32_t p) const { return Pos{int32_t(clamp64(p, 0, n - 1))}; }
+  __device__ static Pos from_lane(const Pos& k, int r, int lanes) { return Pos{__shfl(k.p, r, lanes)}; }
+  __device__ Item fetch(const Pos& k, int c) const {
     // each source row is read once per call: streaming (non-temporal)
     // loads, as for the output rows below (1e7-node batch, K / V indices 0.41 /
     // 0.43 -> 0.39 / 0.41 ms; the large batch's V index 1.30 -> 1.21 ms)
     Item it;
-    Raw<T, VE> r;
-    r.template load<true>(src + clamp64(occ[j], 0, n - 1) * D + c * VE);
-    r.unpack(it.x);
+    it.r.template load<true>(src + int64_t(k.p) * D + c * VE);
     return it;
   }
   __device__ void add(double (&acc)[VE], const Item& it) const {
+    float x[VE];
+    it.r.unpack(x);
 #pragma unroll
-    for (int t = 0; t < VE; ++t) acc[t] += double(it.x[t]);
+    for (int t = 0; t < VE; ++t) acc[t] += double(x[t]);
   }
 };
 
 template <typename T, int VE>
 struct ScaledRows {
-  static constexpr int PIECE_UNROLL = IA_UNROLL;
+  static constexpr int PIECE_UNROLL = 8, ROW_UNROLL = 4;
   const T* __restrict__ src;          // [N, H, dh]
-  const float* __restrict__ occ_scal; // [n, H], occurrence order
-  const int32_t* __restrict__ occ_seg;// [n], occurrence order
+  const int32_t* __restrict__ rec;    // [n, 1 + H]: segment, coefficients
   int D, H, dh;
-  int64_t N;
+  int64_t n, N;
   int h0, h1, split;                  // heads of the chunk; elements t < split use h0
+  struct Pos {
+    int32_t p, v;
+  };
   struct Item {
-    float x[VE];
+    Raw<T, VE> r;
     float s0, s1;
   };
   __device__ void chunk(int c) {
@@ -514,34 +564,65 @@ struct ScaledRows {
     h1 = (c0 + VE - 1) / dh;
     split = (h0 + 1) * dh - c0;
   }
-  __device__ Item fetch(const int32_t* __restrict__, int64_t j, int c) const {
-    const int64_t v = clamp64(occ_seg[j], 0, N - 1);
+  __device__ Pos pos(int32_t p) const {
+    const int32_t e = int32_t(clamp64(p, 0, n - 1));
+    return Pos{e, rec[int64_t(e) * (1 + H)]};
+  }
+  __device__ static Pos from_lane(const Pos& k, int r, int lanes) {
+    return Pos{__shfl(k.p, r, lanes), __shfl(k.v, r, lanes)};
+  }
+  __device__ Item fetch(const Pos& k, int c) const {
     Item it;
-    VecIO<T, VE>::load(src + v * D + c * VE, it.x);
-    it.s0 = occ_scal[j * H + h0];
-    it.s1 = occ_scal[j * H + h1];
+    it.r.template load<false>(src + int64_t(k.v) * D + c * VE);
+    const int32_t* __restrict__ s = rec + int64_t(k.p) * (1 + H) + 1;
+    it.s0 = __int_as_float(s[h0]);
+    it.s1 = dh % VE ? __int_as_float(s[h1]) : it.s0;
     return it;
   }
   __device__ void add(double (&acc)[VE], const Item& it) const {
+    float x[VE];
+    it.r.unpack(x);
 #pragma unroll
-    for (int t = 0; t < VE; ++t) acc[t] = fma(double(t < split ? it.s0 : it.s1), double(it.x[t]), acc[t]);
+    for (int t = 0; t < VE; ++t) acc[t] = fma(double(t < split ? it.s0 : it.s1), double(x[t]), acc[t]);
   }
 };
 
-// acc += the contributions of positions occ[j0 .. j1) in order, chunk c;
-// IA_UNROLL positions are fetched before they are added (in the same order).
-template <int VE, class Src, int U = IA_UNROLL>
-__device__ __forceinline__ void ia_sum(const int32_t* __restrict__ occ, int64_t j0, int64_t j1,
-                                       int c, const Src& src, double (&acc)[VE]) {
-  int64_t j = j0;
-  for (; j + U <= j1; j += U) {
-    typename Src::Item x[U];
+// acc += the contributions of positions occ[j0 .. j1) in order, chunk c of
+// the group's lane l (on: the lane holds a chunk); every lane of the group
+// calls it.  The group's lanes look up a position each -- one load, whatever
+// its count -- and then pass them round, so that the rows of U positions are
+// in flight together, also where a row has fewer than U of them.  In groups
+// of fewer than 8 lanes (rows of a few elements) every lane looks up all.
+template <int VE, class Src, int U>
+__device__ __forceinline__ void ia_sum(const int32_t* __restrict__ occ, int64_t j0, int64_t j1, int c,
+                                       bool on, int l, int lanes, const Src& src, double (&acc)[VE]) {
+  if (lanes < 8) {
+    for (int64_t j = j0; j < j1; j += U) {
+      typename Src::Item x[U];
 #pragma unroll
-    for (int r = 0; r < U; ++r) x[r] = src.fetch(occ, j + r, c);
+      for (int r = 0; r < U; ++r)
+        if (on && j + r < j1) x[r] = src.fetch(src.pos(occ[j + r]), c);
 #pragma unroll
-    for (int r = 0; r < U; ++r) src.add(acc, x[r]);
+      for (int r = 0; r < U; ++r)
+        if (j + r < j1) src.add(acc, x[r]);
+    }
+    return;
   }
-  for (; j < j1; ++j) src.add(acc, src.fetch(occ, j, c));
+  for (int64_t jb = j0; jb < j1; jb += lanes) {
+    const int m = int(j1 - jb < lanes ? j1 - jb : lanes);
+    const typename Src::Pos mine = src.pos(occ[jb + (l < m ? l : m - 1)]);
+    for (int r0 = 0; r0 < m; r0 += U) {
+      typename Src::Item x[U];
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const typename Src::Pos k = Src::from_lane(mine, (r0 + r) & (lanes - 1), lanes);
+        if (on && r0 + r < m) x[r] = src.fetch(k, c);
+      }
+#pragma unroll
+      for (int r = 0; r < U; ++r)
+        if (r0 + r < m) src.add(acc, x[r]);
+    }
+  }
 }
 
 // Pieces of the long rows: one group of `lanes` lanes per piece q in
@@ -569,14 +650,17 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_pieces(
   const int64_t j0 = clamp64(r0 + k * len, r0, r1);
   const int64_t j1 = j0 + len < r1 ? j0 + len : r1;
   const int chunks = D / VE;
-  for (int c = l; c < chunks; c += lanes) {
-    src.chunk(c);
+  for (int c0 = 0; c0 < chunks; c0 += lanes) {
+    const int c = c0 + l;
+    const bool on = c < chunks;
+    src.chunk(on ? c : 0);
     double acc[VE];
 #pragma unroll
     for (int t = 0; t < VE; ++t) acc[t] = 0.0;
-    ia_sum<VE, Src, Src::PIECE_UNROLL>(occ, j0, j1, c, src, acc);
+    ia_sum<VE, Src, Src::PIECE_UNROLL>(occ, j0, j1, c, on, l, lanes, src, acc);
 #pragma unroll
-    for (int t = 0; t < VE; ++t) partial[q * D + c * VE + t] = acc[t];
+    for (int t = 0; t < VE; ++t)
+      if (on) partial[q * D + c * VE + t] = acc[t];
   }
 }
 
@@ -617,83 +701,144 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_groups(
   }
 }
 
-// One group per row: a short row sums its occurrences directly (zeros for
-// none), a long row adds its group sums (or, with few pieces, its piece sums)
-// in order.  fp64 sums, rounded once to fp32.
-template <int VE, class Src>
+// Rounds a row's sum once and stores its chunk.  Output rows are written
+// once: streamed (scaled sums of the large batch's V index 1.61 -> 1.46 ms
+// with both policies).
+template <int VE>
+__device__ __forceinline__ void ia_store(float* __restrict__ dst, const double (&acc)[VE]) {
+  float o[VE];
+#pragma unroll
+  for (int t = 0; t < VE; ++t) o[t] = float(acc[t]);
+  if constexpr (VE == 8) {
+    StreamIO<float, 4, true>::store(dst, o);
+    StreamIO<float, 4, true>::store(dst + 4, o + 4);
+  } else {
+    StreamIO<float, VE, true>::store(dst, o);
+  }
+}
+
+// Chunk c of a long row, added from the level below: its groups, or its
+// pieces (ranges clamped: the counts of malformed lists may wrap).
+template <int VE>
+__device__ __forceinline__ void ia_long_row(
+    const int32_t* __restrict__ multi_off, const int32_t* __restrict__ group_off, int64_t u,
+    int64_t multi_bound, int64_t group_bound, int c, int D, const double* __restrict__ partial,
+    const double* __restrict__ partial2, float* __restrict__ dst) {
+  int64_t p0 = clamp64(group_off[u], 0, group_bound);
+  int64_t p1 = clamp64(group_off[u + 1], p0, group_bound);
+  const double* __restrict__ part = partial2;
+  if (p1 == p0) {
+    p0 = clamp64(multi_off[u], 0, multi_bound);
+    p1 = clamp64(multi_off[u + 1], p0, multi_bound);
+    part = partial;
+  }
+  double acc[VE];
+#pragma unroll
+  for (int t = 0; t < VE; ++t) acc[t] = 0.0;
+  ia_sum_partials<VE, IA_PART_UNROLL>(part, p0, p1, D, c, acc);
+  ia_store<VE>(dst + u * D + c * VE, acc);
+}
+
+// R consecutive rows by one group of lanes: zeros for a row without
+// occurrences, a long row added from the level below.  The rows' occurrences
+// lie side by side in occ, so with R > 1 the group walks them as one stream: the lanes look up as many positions at
+// once as there are lanes, ROW_UNROLL source rows are in flight whichever
+// output rows they belong to, and a row's sum is stored where its last
+// position has been added.  A row of one or two positions by itself waits
+// for offset, position, segment and row one after the other: with 1 / 2 / 4 /
+// 8 rows per group the fp32 sums of 0.44 M and 0.58 M rows (half of 2.64 M
+// positions in hub rows) took 174 / 141 / 125 / 131 and 218 / 169 / 146 / 151
+// us.  A group that meets a long row goes row by row.
+template <int VE, class Src, int R>
 __global__ void __launch_bounds__(IA_THREADS) k_ia_rows(
     const int32_t* __restrict__ occ_off, const int32_t* __restrict__ occ,
     const int32_t* __restrict__ multi_off, const int32_t* __restrict__ group_off,
     int64_t num_rows, int64_t multi_bound, int64_t group_bound, int64_t n, int lanes, int D,
     Src src, const double* __restrict__ partial, const double* __restrict__ partial2,
     float* __restrict__ dst) {
-  const int64_t u = (int64_t(blockIdx.x) * IA_THREADS + threadIdx.x) / lanes;
+  const int64_t u0 = (int64_t(blockIdx.x) * IA_THREADS + threadIdx.x) / lanes * R;
   const int l = int(threadIdx.x) % lanes;
-  if (u >= num_rows) return;
-  const int64_t j0 = clamp64(occ_off[u], 0, n);
-  const int64_t j1 = clamp64(occ_off[u + 1], j0, n);
-  // piece and group ranges clamped too: the counts of malformed lists may wrap
-  const int64_t m0 = clamp64(multi_off[u], 0, multi_bound);
-  const int64_t m1 = clamp64(multi_off[u + 1], m0, multi_bound);
-  const int64_t g0 = clamp64(group_off[u], 0, group_bound);
-  const int64_t g1 = clamp64(group_off[u + 1], g0, group_bound);
-  const bool longrow = ia_multi_pieces(j1 - j0) > 0;
-  // a long row's sums of the level below: its groups, or its pieces
-  const bool grouped = g1 > g0;
-  const double* __restrict__ part = grouped ? partial2 : partial;
-  const int64_t p0 = grouped ? g0 : m0, p1 = grouped ? g1 : m1;
+  if (u0 >= num_rows) return;
+  const int nr = int(num_rows - u0 < R ? num_rows - u0 : R);
   const int chunks = D / VE;
-  for (int c = l; c < chunks; c += lanes) {
-    src.chunk(c);
+  bool stream = false;
+  int64_t lo = 0, hi = 0;                       // lane l < nr: the bounds of row l
+  if constexpr (R > 1) {                        // then lanes > R
+    lo = clamp64(occ_off[u0 + (l < nr ? l : nr)], 0, n);
+    hi = clamp64(occ_off[u0 + (l + 1 < nr ? l + 1 : nr)], 0, n);
+    // every row short and in order: any other sends the group row by row
+    bool bad = hi < lo || hi - lo > IA_PIECE;
+    for (int o = 1; o < lanes; o <<= 1) bad |= __shfl_xor(int(bad), o, lanes) != 0;
+    stream = !bad;
+  }
+  if (!stream) {
+    for (int64_t u = u0; u < u0 + nr; ++u) {
+      const int64_t j0 = clamp64(occ_off[u], 0, n);
+      const int64_t j1 = clamp64(occ_off[u + 1], j0, n);
+      const bool longrow = j1 - j0 > IA_PIECE;
+      for (int c0 = 0; c0 < chunks; c0 += lanes) {
+        const int c = c0 + l;
+        const bool on = c < chunks;
+        if (longrow) {
+          if (on)
+            ia_long_row<VE>(multi_off, group_off, u, multi_bound, group_bound, c, D, partial, partial2,
+                            dst);
+          continue;
+        }
+        src.chunk(on ? c : 0);
+        double acc[VE];
+#pragma unroll
+        for (int t = 0; t < VE; ++t) acc[t] = 0.0;
+        ia_sum<VE, Src, Src::ROW_UNROLL>(occ, j0, j1, c, on, l, lanes, src, acc);
+        if (on) ia_store<VE>(dst + u * D + c * VE, acc);
+      }
+    }
+    return;
+  }
+  const int64_t j0 = __shfl(lo, 0, lanes);
+  const int ends = int(hi - j0);                            // lane r: end of row r, from the first position
+  const int total = __shfl(ends, nr - 1, lanes);            // at most R * IA_PIECE
+  for (int c0 = 0; c0 < chunks; c0 += lanes) {
+    const int c = c0 + l;
+    const bool on = c < chunks;
+    src.chunk(on ? c : 0);
     double acc[VE];
 #pragma unroll
     for (int t = 0; t < VE; ++t) acc[t] = 0.0;
-    if (!longrow)
-      ia_sum<VE>(occ, j0, j1, c, src, acc);
-    else
-      ia_sum_partials<VE, IA_UNROLL>(part, p0, p1, D, c, acc);
-    float o[VE];
+    int row = 0, end = __shfl(ends, 0, lanes);
+    float* out = dst + u0 * D + c * VE;
+    for (int b = 0; b < total; b += lanes) {
+      const int m = total - b < lanes ? total - b : lanes;
+      const typename Src::Pos mine = src.pos(occ[j0 + b + (l < m ? l : m - 1)]);
+      for (int r0 = 0; r0 < m; r0 += Src::ROW_UNROLL) {
+        typename Src::Item x[Src::ROW_UNROLL];
 #pragma unroll
-    for (int t = 0; t < VE; ++t) o[t] = float(acc[t]);
-    // output rows are written once: streamed (scaled sums of the large
-    // batch's V index 1.61 -> 1.46 ms with both policies)
-    if constexpr (VE == 8) {
-      StreamIO<float, 4, true>::store(dst + u * D + c * VE, o);
-      StreamIO<float, 4, true>::store(dst + u * D + c * VE + 4, o + 4);
-    } else {
-      StreamIO<float, VE, true>::store(dst + u * D + c * VE, o);
+        for (int r = 0; r < Src::ROW_UNROLL; ++r) {
+          const typename Src::Pos k = Src::from_lane(mine, (r0 + r) & (lanes - 1), lanes);
+          if (on && r0 + r < m) x[r] = src.fetch(k, c);
+        }
+#pragma unroll
+        for (int r = 0; r < Src::ROW_UNROLL; ++r) {
+          if (r0 + r < m) {
+            while (b + r0 + r == end) {                     // the rows that end before this position
+              if (on) ia_store<VE>(out, acc);
+#pragma unroll
+              for (int t = 0; t < VE; ++t) acc[t] = 0.0;
+              out += D;
+              end = __shfl(ends, ++row, lanes);
+            }
+            src.add(acc, x[r]);
+          }
+        }
+      }
+    }
+    for (; row < nr; ++row) {
+      if (on) ia_store<VE>(out, acc);
+#pragma unroll
+      for (int t = 0; t < VE; ++t) acc[t] = 0.0;
+      out += D;
     }
   }
-}
-
-// seg[e] = the segment v with off[v] <= e < off[v + 1]: a binary search in
-// the offsets per edge, in edge order (neighbouring threads walk the same
-// path); clamped into [0, N) whatever the offsets hold.
-__global__ void __launch_bounds__(IA_THREADS) k_edge_seg(const int32_t* __restrict__ off,
-                                                        int64_t N, int64_t n,
-                                                        int32_t* __restrict__ seg) {
-  const int64_t e = int64_t(blockIdx.x) * IA_THREADS + threadIdx.x;
-  if (e >= n) return;
-  int64_t lo = 0, hi = N - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (int64_t(off[mid]) <= e) lo = mid; else hi = mid - 1;
-  }
-  seg[e] = int32_t(lo);
-}
-
-// Occurrence order for the scaled sums: for every valid occurrence j (below
-// occ_off[num_rows]) of edge e = occ[j], occ_seg[j] = seg[e] and
-// occ_scal[j, :] = scal[e, :] (positions clamped into range).
-__global__ void __launch_bounds__(IA_THREADS) k_coef_permute(
-    const int32_t* __restrict__ occ, const int32_t* __restrict__ occ_off, int64_t num_rows,
-    int64_t n, const int32_t* __restrict__ seg, const float* __restrict__ scal, int H,
-    int32_t* __restrict__ occ_seg, float* __restrict__ occ_scal) {
-  const int64_t j = int64_t(blockIdx.x) * IA_THREADS + threadIdx.x;
-  if (j >= clamp64(occ_off[num_rows], 0, n)) return;
-  const int64_t e = clamp64(occ[j], 0, n - 1);
-  occ_seg[j] = seg[e];
-  for (int h = 0; h < H; ++h) occ_scal[j * H + h] = scal[e * H + h];
 }
 
 struct IaWs {
@@ -788,8 +933,7 @@ extern "C" fast_status_t fast_occurrence_csr(const int32_t* index, int64_t n, in
     shift += width;
   }
   // row offsets from the sorted keys
-  hipLaunchKernelGGL(k_occ_offsets, dim3(uint32_t((num_rows + OO_ROWS) / OO_ROWS)),
-                     dim3(OO_THREADS), 0, st, w.keys[(passes - 1) & 1], n, num_rows, occ_off);
+  launch_lower_bounds(w.keys[(passes - 1) & 1], n, 0, num_rows + 1, OutBound{occ_off}, st);
   return check_launch(fn);
 }
 
@@ -809,17 +953,26 @@ static hipError_t ia_launch(const int32_t* occ_off, const int32_t* occ, int64_t 
   const int64_t mb = ia_multi_bound(n), gb = ia_group_bound(n);
   const int64_t np_blocks = (mb + groups_per_block - 1) / groups_per_block;
   const int64_t ng_blocks = (gb + groups_per_block - 1) / groups_per_block;
-  const int64_t nr_blocks = (num_rows + groups_per_block - 1) / groups_per_block;
-  if (n > 0) {
+  // IA_ROWS rows per group where that leaves the chip enough groups (below,
+  // a group per row fills it better) and a group has a lane for each bound
+  const bool many = lanes >= 4 * IA_ROWS && num_rows >= IA_ROWS * IA_GROUPS_FILL;
+  const int R = many ? IA_ROWS : 1;
+  const int64_t nr_blocks = ((num_rows + R - 1) / R + groups_per_block - 1) / groups_per_block;
+  if (n > IA_PIECE) {
     hipLaunchKernelGGL((k_ia_pieces<VE, Src>), dim3(uint32_t(np_blocks)), dim3(IA_THREADS), 0, st,
                        occ_off, occ, w.multi_off, num_rows, mb, n, lanes, D, src, w.partial);
     hipLaunchKernelGGL((k_ia_groups<VE>), dim3(uint32_t(ng_blocks)), dim3(IA_THREADS), 0, st,
                        occ_off, w.multi_off, w.group_off, num_rows, mb, gb, n, lanes, D, w.partial,
                        w.partial2);
   }
-  hipLaunchKernelGGL((k_ia_rows<VE, Src>), dim3(uint32_t(nr_blocks)), dim3(IA_THREADS), 0, st,
-                     occ_off, occ, w.multi_off, w.group_off, num_rows, mb, gb, n, lanes, D, src,
-                     w.partial, w.partial2, dst);
+  if (many)
+    hipLaunchKernelGGL((k_ia_rows<VE, Src, IA_ROWS>), dim3(uint32_t(nr_blocks)), dim3(IA_THREADS), 0,
+                       st, occ_off, occ, w.multi_off, w.group_off, num_rows, mb, gb, n, lanes, D, src,
+                       w.partial, w.partial2, dst);
+  else
+    hipLaunchKernelGGL((k_ia_rows<VE, Src, 1>), dim3(uint32_t(nr_blocks)), dim3(IA_THREADS), 0, st,
+                       occ_off, occ, w.multi_off, w.group_off, num_rows, mb, gb, n, lanes, D, src,
+                       w.partial, w.partial2, dst);
   return hipGetLastError();
 }
 
@@ -882,14 +1035,10 @@ extern "C" fast_status_t fast_index_add_rows(const int32_t* occ_off, const int32
   return check_launch(fn);
 }
 
-static size_t ias_layout(int64_t n, int64_t num_rows, int H, int D, char* base, int32_t** seg,
-                         int32_t** occ_seg, float** occ_scal, IaWs* ws) {
-  const size_t seg_bytes = align_up(size_t(n) * 4, 256);
-  const size_t scal_bytes = align_up(size_t(n) * size_t(H) * 4, 256);
-  if (seg) *seg = reinterpret_cast<int32_t*>(base);
-  if (occ_seg) *occ_seg = reinterpret_cast<int32_t*>(base + seg_bytes);
-  if (occ_scal) *occ_scal = reinterpret_cast<float*>(base + 2 * seg_bytes);
-  const size_t head = 2 * seg_bytes + scal_bytes;
+static size_t ias_layout(int64_t n, int64_t num_rows, int H, int D, char* base, int32_t** rec,
+                         IaWs* ws) {
+  const size_t head = align_up(size_t(n) * size_t(1 + H) * 4, 256);
+  if (rec) *rec = reinterpret_cast<int32_t*>(base);
   return head + ia_layout(n, num_rows, D, base ? base + head : nullptr, ws);
 }
 
@@ -898,7 +1047,7 @@ extern "C" size_t fast_index_add_scaled_rows_workspace(int64_t n, int64_t num_ro
   const int D = H * dh;
   if (n < 0 || num_rows < 0 || n >= (int64_t(1) << 31) || num_rows >= (int64_t(1) << 31) - 1)
     return 0;
-  return ias_layout(n, num_rows, H, D, nullptr, nullptr, nullptr, nullptr, nullptr);
+  return ias_layout(n, num_rows, H, D, nullptr, nullptr, nullptr);
 }
 
 extern "C" fast_status_t fast_index_add_scaled_rows(
@@ -927,20 +1076,15 @@ extern "C" fast_status_t fast_index_add_scaled_rows(
     return fail(FAST_ERR_UNSUPPORTED, "%s: src/dst/scal misaligned", fn);
   const int VE = ia_vector(D, dh, src, esz, dst);   // a chunk spans at most two heads
   hipStream_t st = static_cast<hipStream_t>(stream);
-  int32_t *seg = nullptr, *occ_seg = nullptr;
-  float* occ_scal = nullptr;
+  int32_t* rec = nullptr;
   IaWs w;
-  ias_layout(n, num_rows, H, D, static_cast<char*>(ws), &seg, &occ_seg, &occ_scal, &w);
-  if (n > 0) {
-    const dim3 grid{uint32_t((n + IA_THREADS - 1) / IA_THREADS)};
-    hipLaunchKernelGGL(k_edge_seg, grid, dim3(IA_THREADS), 0, st, dst_offsets, num_dst, n, seg);
-    hipLaunchKernelGGL(k_coef_permute, grid, dim3(IA_THREADS), 0, st, occ, occ_off, num_rows, n, seg,
-                       scal, H, occ_seg, occ_scal);
-  }
+  ias_layout(n, num_rows, H, D, static_cast<char*>(ws), &rec, &w);
+  if (n > 0)
+    launch_lower_bounds(dst_offsets, num_dst, 1, n, OutEdgeRec{scal, rec, H, int32_t(num_dst - 1)}, st);
   hipError_t e = hipSuccess;
 #define FAST_IAS(T_, VE_)                                                                          \
   e = ia_launch<VE_>(occ_off, occ, n, num_rows, D,                                                 \
-                     ScaledRows<T_, VE_>{static_cast<const T_*>(src), occ_scal, occ_seg, D, H, dh, \
+                     ScaledRows<T_, VE_>{static_cast<const T_*>(src), rec, D, H, dh, n,             \
                                          num_dst, 0, 0, 0},                                        \
                      w, dst, st)
   if (src_dtype == FAST_F32) {

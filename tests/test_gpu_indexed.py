@@ -392,3 +392,33 @@ def test_indexed_coefficients_and_row_gradients(cfg, i):
         assert_close(rows_grad, want, "f32", f"{what} d{name} rows")
     del o, dQ, ge, ae
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (4, 32, "bf16"), (1, 16, "f32"), (5, 64, "f32"), (3, 20, "bf16")])
+@pytest.mark.parametrize("rows", [65_535, 65_536, 65_539])
+def test_row_sums_of_large_outputs(H, dh, dt, rows):
+    """Outputs of 65,536 rows and more are summed several rows to a group of lanes (narrow rows of fewer
+    than 16 lanes, and smaller outputs, one to a group): rows of 0, 1, 2, a few, 63, 64 and 65
+    positions and a hub side by side, the last group incomplete, plain and scaled sums."""
+    _announce(f"row sums of a large output rows={rows} H={H} dh={dh} {dt}")
+    r = np.random.default_rng(rows + H * dh)
+    cnt = r.choice([0, 1, 2, 3, 9], rows, p=[0.3, 0.35, 0.2, 0.1, 0.05])
+    cnt[[0, 1, 5, 6, 4000, rows - 1]] = [0, 64, 63, 65, 5000, 2]
+    idx = np.repeat(np.arange(rows), cnt).astype(np.int32)
+    r.shuffle(idx)
+    n = idx.size
+    off, occ = _occ_gpu(idx, rows)
+    src = _randn((n, H * dh), dt, "cuda", rows + H)
+    assert_close(_index_add_gpu(off, occ, n, rows, src), oracle.index_add_rows(idx, rows, _host(src)), "f32",
+                 "large plain sums")
+    deg = r.integers(0, 9, n // 4 + 1).astype(np.int64)
+    dst_off = np.minimum(np.concatenate([[0], np.cumsum(deg)]), n).astype(np.int32)
+    dst_off[-1] = n
+    N = dst_off.size - 1
+    scal, q = _randn((n, H), "f32", "cuda", 5), _randn((N, H, dh), dt, "cuda", 6)
+    got = _scaled_rows_gpu(off, occ, n, rows, to_dev(dst_off), N, H, dh, scal, q)
+    assert_close(got, oracle.index_add_scaled_rows(idx, dst_off, rows, scal.cpu().numpy(), _host(q)), "f32",
+                 "large scaled sums")
+    bad = off.clone()                       # malformed lists of this size stay in bounds too
+    bad[::7] = torch.as_tensor(r.integers(-5, n + 6, bad[::7].numel()).astype(np.int32), device="cuda")
+    assert torch.equal(_index_add_gpu(bad, occ, n, rows, src), _index_add_gpu(bad, occ, n, rows, src))
