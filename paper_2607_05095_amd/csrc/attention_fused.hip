@@ -134,12 +134,10 @@ fast_status_t attn_run(const char* fn, Op op, const fast_tcsr_t* g, int H, int d
     return fail(FAST_ERR_INVALID_ARG, "%s: K/V row stride %lld is not a multiple of F = %d", fn,
                 (long long)a.ldkv, a.L.F);
   // fp32 rows whose heads break the 16-byte alignment (dh % 4 != 0) but whose
-  // width does not (F % 4 == 0): the fused operators use row-major lanes so
-  // every row moves as 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).
-  const bool fused_op = op == Op::kAttnFwd || op == Op::kAttnBwd || op == Op::kAttnFwdIdx ||
-                        op == Op::kAttnBwdIdx;
+  // width does not (F % 4 == 0): row-major lanes, so every row moves as
+  // 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).
   a.L.rm = false;
-  if (fused_op && rowmajor_enabled() && dt == FAST_F32 && H == 2 && dh % 4 != 0 &&
+  if (rowmajor_enabled() && dt == FAST_F32 && H == 2 && dh % 4 != 0 &&
       (H * dh) % 4 == 0 && (H * dh) / 4 <= 64) {
     bool al = true;
     for (int k = 0; k < nrows; ++k)

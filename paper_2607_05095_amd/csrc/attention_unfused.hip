@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "attention.h"
+#include "attention_rowmajor_unfused.h"
 
 namespace fast {
 
@@ -18,8 +19,29 @@ static void launch_unfused(Op op, const AttnArgs& a, dim3 grid, dim3 block, hipS
   }
 }
 
+template <int H, int G>
+static void launch_unfused_rm(Op op, const AttnArgs& a, dim3 grid, dim3 block, hipStream_t st) {
+  switch (op) {
+    case Op::kSoftmaxFwd: hipLaunchKernelGGL((k_softmax_fwd_rm<H, G>), grid, block, 0, st, a); break;
+    case Op::kSoftmaxBwd: hipLaunchKernelGGL((k_softmax_bwd_rm<H, G>), grid, block, 0, st, a); break;
+    case Op::kAggFwd: hipLaunchKernelGGL((k_agg_fwd_rm<H, G>), grid, block, 0, st, a); break;
+    case Op::kAggBwd: hipLaunchKernelGGL((k_agg_bwd_rm<H, G>), grid, block, 0, st, a); break;
+    default: break;
+  }
+}
+
 bool attn_launch_unfused(Op op, fast_dtype_t dt, const AttnArgs& a, dim3 grid, dim3 block,
                          hipStream_t st) {
+  if (a.L.rm) {
+#define FAST_TRY_RM(H_, G_)                                   \
+  if (a.L.H == H_ && a.L.G == G_) {                           \
+    launch_unfused_rm<H_, G_>(op, a, grid, block, st);        \
+    return true;                                              \
+  }
+    FAST_ATTN_RM_SET(FAST_TRY_RM)
+#undef FAST_TRY_RM
+    return false;
+  }
   const bool bf = dt == FAST_BF16;
   const int VE = a.L.VE, P = a.L.P, LPH = a.L.LPH;
 #define FAST_TRY(T_, VE_, P_, L_)                                                     \
