@@ -17,7 +17,9 @@
 //   * Softmax is computed online over chunks of CH edges (one rescale per
 //     chunk) in base 2, so any degree works and a segment is streamed once.
 //     The loads of a chunk are issued back to back; slots past the segment
-//     end re-read its last row (a cache hit) and are masked out.
+//     end load nothing and are masked out (re-reading the segment's last row
+//     instead cost its requests: 120,001 ragged segments of 3.6 edges on
+//     average, fp32 2 x 64 heads, forward 136 -> 102 us; full chunks the same).
 //   * Every destination row is produced by exactly one sub-wavefront: the
 //     results are deterministic run to run (unlike the paper's edge-parallel
 //     atomicAdd aggregation, which is prior art for a different GPU).
@@ -290,10 +292,17 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd(AttnArg
     Raw<T, VE> kr[ATT_CH_FWD][P], vr[ATT_CH_FWD][P];
 #pragma unroll
     for (int i = 0; i < ATT_CH_FWD; ++i) {
-      const int64_t e = slot_row(base, i, e1);
-      // indexed rows are shared across segments: keep them cacheable
-      load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
-      load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        kr[i][p].zero();
+        vr[i][p].zero();
+      }
+      if (base + i < e1) {
+        const int64_t e = base + i;
+        // indexed rows are shared across segments: keep them cacheable
+        load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
+        load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
+      }
     }
     float t[ATT_CH_FWD];
     float cm = -INFINITY;
