@@ -16,10 +16,16 @@
 //     chunk are straight-line code the scheduler interleaves.
 //   * Softmax is computed online over chunks of CH edges (one rescale per
 //     chunk) in base 2, so any degree works and a segment is streamed once.
-//     The loads of a chunk are issued back to back; slots past the segment
-//     end load nothing and are masked out (re-reading the segment's last row
-//     instead cost its requests: 120,001 ragged segments of 3.6 edges on
-//     average, fp32 2 x 64 heads, forward 136 -> 102 us; full chunks the same).
+//     The loads of a chunk are issued back to back.  A slot that no segment
+//     of the wave needs is skipped by a uniform branch; otherwise slots past
+//     a segment's end re-read its last row (a cache hit) and are masked out.
+//     Re-reading alone costs requests on short segments, and a load per
+//     segment under its own mask breaks up the batch of loads.  Re-read /
+//     masked / skipped, layer of 100,000 segments, us: forward of ragged
+//     fp32 4 x 32 (3.6 edges on average) 89 / 61 / 61, forward and backward
+//     of ragged fp32 2 x 50 321 / 408 / 308, of ragged bf16 2 x 50 148 / 191 /
+//     136; full chunks the same with all but the mask (fp32 2 x 50, 2.64 M
+//     edges: 1161 / 1185 / 1157).
 //   * Every destination row is produced by exactly one sub-wavefront: the
 //     results are deterministic run to run (unlike the paper's edge-parallel
 //     atomicAdd aggregation, which is prior art for a different GPU).
@@ -292,13 +298,14 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd(AttnArg
     Raw<T, VE> kr[ATT_CH_FWD][P], vr[ATT_CH_FWD][P];
 #pragma unroll
     for (int i = 0; i < ATT_CH_FWD; ++i) {
+      if (!__any(base + i < e1)) {
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        kr[i][p].zero();
-        vr[i][p].zero();
-      }
-      if (base + i < e1) {
-        const int64_t e = base + i;
+        for (int p = 0; p < P; ++p) {
+          kr[i][p].zero();
+          vr[i][p].zero();
+        }
+      } else {
+        const int64_t e = slot_row(base, i, e1);
         // indexed rows are shared across segments: keep them cacheable
         load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
         load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
@@ -366,9 +373,17 @@ __device__ __forceinline__ void bwd_chunk(const AttnArgs& a, const LaneMap<P>& m
   Raw<T, VE> kr[ATT_CH_BWD][P], vr[ATT_CH_BWD][P];
 #pragma unroll
   for (int i = 0; i < ATT_CH_BWD; ++i) {
-    const int64_t e = slot_row(base, i, e1);
-    load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
-    load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
+    if (!__any(base + i < e1)) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        kr[i][p].zero();
+        vr[i][p].zero();
+      }
+    } else {
+      const int64_t e = slot_row(base, i, e1);
+      load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
+      load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
+    }
   }
   float t[ATT_CH_BWD], cm = -INFINITY;
 #pragma unroll
@@ -510,7 +525,88 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_bwd(AttnArg
   }
 }
 
+// ============================================================ separate operators
+// Rows [base, min(base + CH, e1)) of a per-edge array; slots past the end hold
+// the segment's last row again, or zeros where no segment of the wave needs
+// the slot.
+template <typename T, int VE, int P, int CH>
+__device__ __forceinline__ void load_rows(const T* __restrict__ rows, int64_t base, int64_t e1, int F,
+                                          const LaneMap<P>& m, Raw<T, VE> (&x)[CH][P]) {
+  const int64_t last = e1 > 0 ? e1 - 1 : 0;   // also of an empty segment: a row of the array
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    if (!__any(base + i < e1)) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) x[i][p].zero();
+    } else {
+      load_raw<T, VE, P, false>(rows, base + i < e1 ? base + i : last, F, m, x[i]);
+    }
+  }
+}
+
+// The chunk's scalars of a per-edge [E, H] array for the lane's head: entry i
+// lives in lane i % LPH of the head, slot i / LPH (0 past the segment's end),
+// so that a chunk moves as one or a few accesses (with K's single reading,
+// 66,000 segments of 20 edges, bf16 4 x 32: the four operators 610 -> 442 us);
+// get passes an entry to all lanes.  LPH = 0 (lanes per head known at run time only): every lane holds
+// all entries.
+template <int LPH, int CH>
+struct LaneScalars {
+  static constexpr int L = LPH > 0 ? LPH : 1;
+  static constexpr int N = (CH + L - 1) / L;
+  float v[N];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int s = 0; s < N; ++s) v[s] = 0.f;
+  }
+  template <class M>
+  __device__ __forceinline__ void load(const float* __restrict__ p, int64_t base, int64_t e1, int H,
+                                       const M& m) {
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      const int i = s * L + (LPH > 0 ? m.l : 0);
+      v[s] = i < CH && base + i < e1 ? p[(base + i) * H + m.h] : 0.f;
+    }
+  }
+  __device__ __forceinline__ float get(int i) const {
+    if constexpr (LPH > 1) return __shfl(v[i / L], i % L, L);
+    else return v[i];
+  }
+  template <class M>
+  __device__ __forceinline__ void put(int i, float x, const M& m) {
+    v[i / L] = LPH > 0 && m.l != i % L ? v[i / L] : x;
+  }
+  template <class M>
+  __device__ __forceinline__ void store(float* __restrict__ p, int64_t base, int64_t e1, int H,
+                                        const M& m) const {
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      const int i = s * L + (LPH > 0 ? m.l : 0);
+      if (i < CH && base + i < e1 && (LPH > 0 || m.l == 0)) p[(base + i) * H + m.h] = v[s];
+    }
+  }
+};
+
 // ============================================================ edge softmax fwd
+// The logits of the first SM_SAVE chunks stay in registers: a segment of up
+// to 20 edges reads its K rows once.
+constexpr int SM_SAVE = 2;
+
+template <typename T, int VE, int P, int LPH_CT>
+__device__ __forceinline__ void softmax_logits(const T* __restrict__ K, const float (&q)[P][VE],
+                                               const LaneMap<P>& m, int64_t base, int64_t e1, int F,
+                                               float sl2, float slope, float (&t)[ATT_CH_FWD]) {
+  Raw<T, VE> kr[ATT_CH_FWD][P];
+  load_rows<T, VE, P, ATT_CH_FWD>(K, base, e1, F, m, kr);
+#pragma unroll
+  for (int i = 0; i < ATT_CH_FWD; ++i) {
+    float kx[P][VE];
+    unpack_row<T, VE, P>(kr[i], kx);
+    const float ti = lrelu(head_dot<VE, P, LPH_CT>(q, kx, m.lph) * sl2, slope);
+    t[i] = base + i < e1 ? ti : -INFINITY;
+  }
+}
+
 template <typename T, int VE, int P, int LPH_CT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_fwd(AttnArgs a) {
   LaneMap<P> m;
@@ -523,40 +619,52 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_fwd(AttnArgs a) {
   int64_t e0, e1;
   seg_range(a, m.seg, e0, e1);
   float mx = -INFINITY, Z = 0.f;
-  // pass 1: running max and normaliser
-  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
-    float kx[ATT_CH_FWD][P][VE];
+  auto fold = [&](const float (&t)[ATT_CH_FWD]) {
+    float mn = mx;
 #pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) load_row<T, VE, P>(K, slot_row(base, i, e1), F, m, kx[i]);
-    float t[ATT_CH_FWD], cm = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) {
-      const float ti = lrelu(head_dot<VE, P, LPH_CT>(q, kx[i], m.lph) * sl2, a.slope);
-      t[i] = base + i < e1 ? ti : -INFINITY;
-      cm = fmaxf(cm, t[i]);
-    }
-    const float mn = fmaxf(mx, cm);
+    for (int i = 0; i < ATT_CH_FWD; ++i) mn = fmaxf(mn, t[i]);
     Z *= exp2_hw(mx - mn);
 #pragma unroll
     for (int i = 0; i < ATT_CH_FWD; ++i) Z += exp2_hw(t[i] - mn);
     mx = mn;
+  };
+  // pass 1: running max and normaliser
+  float t[SM_SAVE][ATT_CH_FWD];
+#pragma unroll
+  for (int c = 0; c < SM_SAVE; ++c) {
+    const int64_t base = e0 + c * ATT_CH_FWD;
+    if (base < e1) {
+      softmax_logits<T, VE, P, LPH_CT>(K, q, m, base, e1, F, sl2, a.slope, t[c]);
+      fold(t[c]);
+    }
+  }
+  for (int64_t base = e0 + SM_SAVE * ATT_CH_FWD; base < e1; base += ATT_CH_FWD) {
+    float tt[ATT_CH_FWD];
+    softmax_logits<T, VE, P, LPH_CT>(K, q, m, base, e1, F, sl2, a.slope, tt);
+    fold(tt);
   }
   const float invZ = Z > 0.f ? 1.f / Z : 0.f;
   if (a.lse_out && m.l == 0) a.lse_out[m.seg * H + m.h] = Z > 0.f ? (mx + log2f(Z)) * LN2 : -INFINITY;
-  // pass 2: alpha (the segment's K rows are re-read, normally from L2)
-  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
-    float kx[ATT_CH_FWD][P][VE];
+  // pass 2: alpha (past the saved chunks K is read again, normally from L2)
+  auto emit = [&](const float (&x)[ATT_CH_FWD], int64_t base) {
+    LaneScalars<LPH_CT, ATT_CH_FWD> s;
+    s.zero();
 #pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) load_row<T, VE, P>(K, slot_row(base, i, e1), F, m, kx[i]);
+    for (int i = 0; i < ATT_CH_FWD; ++i) s.put(i, exp2_hw(x[i] - mx) * invZ, m);
+    s.store(a.alpha_out, base, e1, H, m);
+  };
 #pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) {
-      const float t = lrelu(head_dot<VE, P, LPH_CT>(q, kx[i], m.lph) * sl2, a.slope);
-      if (base + i < e1 && m.l == 0) a.alpha_out[(base + i) * H + m.h] = exp2_hw(t - mx) * invZ;
-    }
+  for (int c = 0; c < SM_SAVE; ++c)
+    if (e0 + c * ATT_CH_FWD < e1) emit(t[c], e0 + c * ATT_CH_FWD);
+  for (int64_t base = e0 + SM_SAVE * ATT_CH_FWD; base < e1; base += ATT_CH_FWD) {
+    float tt[ATT_CH_FWD];
+    softmax_logits<T, VE, P, LPH_CT>(K, q, m, base, e1, F, sl2, a.slope, tt);
+    emit(tt, base);
   }
 }
 
 // ============================================================ edge softmax bwd
+// The first chunk is loaded before D is known.
 template <typename T, int VE, int P, int LPH_CT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
   LaneMap<P> m;
@@ -567,30 +675,47 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
   load_row<T, VE, P>(static_cast<const T*>(a.Q), m.seg, F, m, q);
   int64_t e0, e1;
   seg_range(a, m.seg, e0, e1);
+  LaneScalars<LPH_CT, ATT_CH_FWD> al, da;
+  Raw<T, VE> kr[ATT_CH_FWD][P];
+  al.load(a.alpha_in, e0, e1, H, m);
+  da.load(a.dalpha_in, e0, e1, H, m);
+  load_rows<T, VE, P, ATT_CH_FWD>(K, e0, e1, F, m, kr);
   float D = 0.f;
-  for (int64_t e = e0; e < e1; ++e) D = fmaf(a.alpha_in[e * H + m.h], a.dalpha_in[e * H + m.h], D);
+#pragma unroll
+  for (int s = 0; s < al.N; ++s) D = fmaf(al.v[s], da.v[s], D);
+  for (int64_t base = e0 + ATT_CH_FWD; base < e1; base += ATT_CH_FWD) {
+    LaneScalars<LPH_CT, ATT_CH_FWD> x, y;
+    x.load(a.alpha_in, base, e1, H, m);
+    y.load(a.dalpha_in, base, e1, H, m);
+#pragma unroll
+    for (int s = 0; s < x.N; ++s) D = fmaf(x.v[s], y.v[s], D);
+  }
+  if constexpr (LPH_CT > 0) D = group_sum_ct<LPH_CT>(D);   // else every lane summed all entries
   float dq[P][VE];
   FAST_ZERO(dq);
-  for (int64_t base = e0; base < e1; base += ATT_CH_BWD) {
-    float kx[ATT_CH_BWD][P][VE];
+  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
+    if (base != e0) {
+      al.load(a.alpha_in, base, e1, H, m);
+      da.load(a.dalpha_in, base, e1, H, m);
+      load_rows<T, VE, P, ATT_CH_FWD>(K, base, e1, F, m, kr);
+    }
 #pragma unroll
-    for (int i = 0; i < ATT_CH_BWD; ++i) load_row<T, VE, P>(K, slot_row(base, i, e1), F, m, kx[i]);
+    for (int s = 0; s < al.N; ++s) al.v[s] *= da.v[s] - D;   // 0 past the segment's end
 #pragma unroll
-    for (int i = 0; i < ATT_CH_BWD; ++i) {
-      const int64_t e = slot_row(base, i, e1);
-      const float pre = head_dot<VE, P, LPH_CT>(q, kx[i], m.lph) * a.scale;
-      const float g = base + i < e1 ? a.alpha_in[e * H + m.h] * (a.dalpha_in[e * H + m.h] - D) *
-                                          lrelu_grad(pre, a.slope) * a.scale
-                                    : 0.f;
-      float dk[P][VE];
+    for (int i = 0; i < ATT_CH_FWD; ++i) {
+      if (base + i >= e1) break;
+      float kx[P][VE], dk[P][VE];
+      unpack_row<T, VE, P>(kr[i], kx);
+      const float pre = head_dot<VE, P, LPH_CT>(q, kx, m.lph) * a.scale;
+      const float g = al.get(i) * lrelu_grad(pre, a.slope) * a.scale;
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int j = 0; j < VE; ++j) {
-          dq[p][j] = fmaf(g, kx[i][p][j], dq[p][j]);
+          dq[p][j] = fmaf(g, kx[p][j], dq[p][j]);
           dk[p][j] = g * q[p][j];
         }
-      if (base + i < e1) store_row<T, VE, P>(static_cast<T*>(a.dK), e, F, m, dk);
+      store_row<T, VE, P>(static_cast<T*>(a.dK), base + i, F, m, dk);
     }
   }
   store_row<T, VE, P>(static_cast<T*>(a.dQ), m.seg, F, m, dq);
@@ -608,19 +733,20 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_fwd(AttnArgs a) {
   float acc[P][VE];
   FAST_ZERO(acc);
   for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
-    float vx[ATT_CH_FWD][P][VE], al[ATT_CH_FWD];
+    LaneScalars<LPH_CT, ATT_CH_FWD> al;
+    Raw<T, VE> vr[ATT_CH_FWD][P];
+    al.load(a.alpha_in, base, e1, H, m);
+    load_rows<T, VE, P, ATT_CH_FWD>(V, base, e1, F, m, vr);
 #pragma unroll
     for (int i = 0; i < ATT_CH_FWD; ++i) {
-      const int64_t e = slot_row(base, i, e1);
-      load_row<T, VE, P>(V, e, F, m, vx[i]);
-      al[i] = base + i < e1 ? a.alpha_in[e * H + m.h] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i)
+      float vx[P][VE];
+      unpack_row<T, VE, P>(vr[i], vx);
+      const float w = al.get(i);
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(al[i], vx[i][p][j], acc[p][j]);
+        for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(w, vx[p][j], acc[p][j]);
+    }
   }
   store_row<T, VE, P>(static_cast<T*>(a.out), m.seg, F, m, acc);
 }
@@ -636,25 +762,25 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_bwd(AttnArgs a) {
   load_row<T, VE, P>(static_cast<const T*>(a.dO), m.seg, F, m, go);
   int64_t e0, e1;
   seg_range(a, m.seg, e0, e1);
-  for (int64_t base = e0; base < e1; base += ATT_CH_BWD) {
-    float vx[ATT_CH_BWD][P][VE];
+  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
+    LaneScalars<LPH_CT, ATT_CH_FWD> al, da;
+    Raw<T, VE> vr[ATT_CH_FWD][P];
+    al.load(a.alpha_in, base, e1, H, m);
+    load_rows<T, VE, P, ATT_CH_FWD>(V, base, e1, F, m, vr);
+    da.zero();
 #pragma unroll
-    for (int i = 0; i < ATT_CH_BWD; ++i) load_row<T, VE, P>(V, slot_row(base, i, e1), F, m, vx[i]);
-#pragma unroll
-    for (int i = 0; i < ATT_CH_BWD; ++i) {
-      const int64_t e = slot_row(base, i, e1);
-      const float da = head_dot<VE, P, LPH_CT>(go, vx[i], m.lph);
-      const float al = a.alpha_in[e * H + m.h];
-      float dv[P][VE];
+    for (int i = 0; i < ATT_CH_FWD; ++i) {
+      float vx[P][VE], dv[P][VE];
+      unpack_row<T, VE, P>(vr[i], vx);
+      da.put(i, head_dot<VE, P, LPH_CT>(go, vx, m.lph), m);
+      const float w = al.get(i);
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int j = 0; j < VE; ++j) dv[p][j] = al * go[p][j];
-      if (base + i < e1) {
-        if (m.l == 0) a.dalpha_out[e * H + m.h] = da;
-        store_row<T, VE, P>(static_cast<T*>(a.dV), e, F, m, dv);
-      }
+        for (int j = 0; j < VE; ++j) dv[p][j] = w * go[p][j];
+      if (base + i < e1) store_row<T, VE, P>(static_cast<T*>(a.dV), base + i, F, m, dv);
     }
+    da.store(a.dalpha_out, base, e1, H, m);
   }
 }
 

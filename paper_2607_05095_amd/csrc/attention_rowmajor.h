@@ -137,9 +137,14 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd_rm(Attn
     // segments and stay cacheable.)
 #pragma unroll
     for (int i = 0; i < RM_CH_FWD; ++i) {
-      const int64_t e = slot_row(base, i, e1);
-      rm_load_row<!IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
-      rm_load_row<!IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+      if (!__any(base + i < e1)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
+      } else {
+        const int64_t e = slot_row(base, i, e1);
+        rm_load_row<!IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
+        rm_load_row<!IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+      }
     }
     float t[RM_CH_FWD][H], cm[H];
 #pragma unroll
@@ -208,9 +213,14 @@ __device__ __forceinline__ void rm_bwd_chunk(const AttnArgs& a, const RmMap<H>& 
   float kx[RM_CH_BWD][4], vx[RM_CH_BWD][4];
 #pragma unroll
   for (int i = 0; i < RM_CH_BWD; ++i) {
-    const int64_t e = slot_row(base, i, e1);
-    rm_load_row<NT && !IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
-    rm_load_row<NT && !IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+    if (!__any(base + i < e1)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
+    } else {
+      const int64_t e = slot_row(base, i, e1);
+      rm_load_row<NT && !IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
+      rm_load_row<NT && !IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+    }
   }
   float t[RM_CH_BWD][H], cm[H];
 #pragma unroll

@@ -4,15 +4,15 @@
 // their rows move as 16-byte accesses too.
 //
 // Each kernel reads or writes its per-edge rows once and is bound by HBM.  A
-// chunk of RU_CH edges is loaded back to back; slots past the segment's end
-// load nothing.  The per-edge scalars of a chunk (alpha, dalpha: RU_CH x H
+// chunk of RU_CH edges is loaded back to back; slots that no segment of the
+// wave needs load nothing.  The per-edge scalars of a chunk (alpha, dalpha: RU_CH x H
 // consecutive floats) move as one access, a lane per float, and are passed
 // between lanes by shuffles.  The softmax keeps the logits of the first
 // RU_SAVE chunks in registers, so that a segment of up to 20 edges reads its
 // K rows once; its backward has the first chunk's rows in flight before it
 // forms D.  66,000 segments of 10 edges, 2 x 50 heads, against the head-major
-// lanes' 8-byte accesses: softmax forward 91 -> 70 us, aggregation forward
-// 59 -> 48, aggregation backward 125 -> 101, softmax backward 145 -> 111 us
+// lanes' 8-byte accesses: softmax forward 91 -> 66 us, aggregation forward
+// 59 -> 48, aggregation backward 125 -> 100, softmax backward 145 -> 109 us
 // (138 with D formed first).
 #pragma once
 
@@ -24,14 +24,16 @@ constexpr int RU_CH = 10;
 constexpr int RU_SAVE = 2;
 
 // Rows [base, min(base + RU_CH, e1)) of a per-edge array, streamed: each is
-// read once per call.  Slots past the end hold zeros.
+// read once per call.  Slots past the end hold the segment's last row again,
+// or zeros where no segment of the wave needs the slot.
 template <int H>
 __device__ __forceinline__ void ru_load(const float* __restrict__ rows, int64_t base, int64_t e1, int F,
                                         const RmMap<H>& m, float (&x)[RU_CH][4]) {
+  const int64_t last = e1 > 0 ? e1 - 1 : 0;   // also of an empty segment: a row of the array
 #pragma unroll
   for (int i = 0; i < RU_CH; ++i) {
-    x[i][0] = x[i][1] = x[i][2] = x[i][3] = 0.f;
-    if (base + i < e1) rm_load_row<true, H>(rows, base + i, F, m, x[i]);
+    if (!__any(base + i < e1)) x[i][0] = x[i][1] = x[i][2] = x[i][3] = 0.f;
+    else rm_load_row<true, H>(rows, base + i < e1 ? base + i : last, F, m, x[i]);
   }
 }
 

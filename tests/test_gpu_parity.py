@@ -219,6 +219,17 @@ def test_attention_edge_cases(name, counts, H, dh, dt):
         assert torch.count_nonzero(fused[0]) == 0 and torch.count_nonzero(fused[2]) == 0
 
 
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (2, 30, "f32"), (2, 102, "f32"), (4, 32, "f32"),
+                                     (4, 32, "bf16"), (3, 13, "f32"), (1, 128, "bf16")])
+def test_attention_chunk_edges(H, dh, dt):
+    """Degrees around the chunks of 4, 5 and 10 edges and the 20 logits the separate softmax keeps, next to
+    segments of other degrees and empty ones (leading ones too) in the same wave; row-major groups
+    of 16, 32 and 64 lanes, head-major heads of 4 to 32 lanes and of lanes known at run time only."""
+    counts = [0, 0, 1, 0, 4, 5, 9, 0, 10, 11, 19, 1, 20, 21, 0, 0, 31, 2, 45, 0, 10, 10, 3, 0]
+    _announce(f"attention chunk edges {H}x{dh} {dt}")
+    _check_block(_synthetic_block(counts, H, dh, dt, seed=dh), None, f"chunk edges {H}x{dh} {dt}")
+
+
 @pytest.mark.parametrize("slope", [-0.3, 0.0])
 @pytest.mark.parametrize("name,counts,H,dh,dt", [
     ("rowmajor_f32", [10, 1, 0, 7, 30, 10, 25, 3, 12], 2, 50, "f32"),
