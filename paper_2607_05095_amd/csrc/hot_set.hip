@@ -4,13 +4,15 @@
 // row reconstruction reads.
 //
 // Counting.  Every batch adds one to the counter of each distinct id it
-// touches.  One launch per batch; each id sets its batch's bit in a byte per
-// id (atomicOr; up to 32 batches, in groups of 8 with a clear per group) or
-// stamps its slot with the batch tag (atomicExch; more batches), and only the
-// access that finds the bit clear or replaces an older tag increments the
-// counter, so repeats inside a batch count once.  Integer atomics make the
-// counts exact whatever the interleaving; an LDS hash per workgroup drops
-// most repeats before they reach HBM.
+// touches.  Dense universes: a byte map per batch, marked with plain stores,
+// then added up.  Sparse universes: ids grouped by bucket, batch bits met in
+// LDS (below).  Universes too large for that, or batches too small for its
+// stages to fit the workspace: one launch per batch; each id sets its batch's
+// bit in a byte per id (atomicOr; up to 32 batches, in groups of 8 with a
+// clear per group) or stamps its slot with the batch tag (atomicExch; more
+// batches), and only the access that finds the bit clear or replaces an older
+// tag increments the counter.  Repeats inside a batch count once; integer
+// sums make the counts exact whatever the interleaving.
 //
 // Selection.  Alg. 1 ranks each kind by descending count and merges the two
 // lists, a node winning only with a strictly higher count.  The ids it takes
@@ -165,15 +167,270 @@ __global__ void __launch_bounds__(HS_THREADS) k_ac_accumulate(const uint32_t* __
   }
 }
 
+// Buckets: an id's marks meet in LDS instead of in a map of the universe in
+// HBM, so counting costs no random atomics with an answer to wait for, and
+// nothing of the universe's size is cleared or swept in memory.
+//   k_ac_stage: a workgroup takes AB_CHUNK ids of one batch, drops repeats in
+//     an LDS hash, and writes the rest to its own stage region grouped by
+//     bucket of 2^bits ids, with the start of every bucket's run in its row of
+//     the run-start table -- each entry the id inside its bucket and the batch's
+//     number within the group of up to AC_GROUP batches.
+//   k_ac_bucket: a workgroup per bucket ORs the batch bits of the bucket's
+//     runs into a byte per id in LDS and adds the popcount of every nonzero
+//     byte to freq, which no other workgroup touches there.
+// Both are bound by LDS operations and by the latency of the runs' short
+// reads; the chunk is as large as LDS allows so that runs are long (16,384
+// ids: about 5 entries of each of 1526 buckets for the 2e8-id universe).
+constexpr int AB_THREADS = 1024;
+constexpr int AB_WAVES = AB_THREADS / 64;
+constexpr int AB_ITEMS = 16;
+constexpr int AB_CHUNK = AB_THREADS * AB_ITEMS;
+constexpr int AB_HASH_BITS = 15;                  // 2 * AB_CHUNK slots: load <= 1/2, probing always ends
+constexpr int AB_MAX_BUCKETS = 2048;
+constexpr int AB_MIN_BITS = 12, AB_MAX_BITS = 17; // 2^bits bytes of LDS per bucket
+static_assert((1 << AB_HASH_BITS) == 2 * AB_CHUNK && AB_CHUNK < 65536, "hash size, 16-bit run starts");
+
+// The batches of one group: ids [begin[k], begin[k] + count[k]) and the chunks
+// [chunk0[k], chunk0[k + 1]) of batch k.
+struct AbBatches {
+  int64_t begin[AC_GROUP], count[AC_GROUP];
+  int32_t chunk0[AC_GROUP + 1];
+  int n;
+};
+
+template <typename E>
+__global__ void __launch_bounds__(AB_THREADS) k_ac_stage(const int64_t* __restrict__ ids, AbBatches bt,
+                                                        int64_t id_bound, int bits, int B,
+                                                        uint16_t* __restrict__ starts,
+                                                        E* __restrict__ stage) {
+  __shared__ uint32_t s_key[1 << AB_HASH_BITS];
+  __shared__ uint32_t s_cnt[AB_MAX_BUCKETS];
+  __shared__ uint32_t s_wave[AB_WAVES];
+  for (int j = threadIdx.x; j < (1 << AB_HASH_BITS); j += AB_THREADS) s_key[j] = HS_EMPTY;
+  for (int j = threadIdx.x; j < AB_MAX_BUCKETS; j += AB_THREADS) s_cnt[j] = 0u;
+  int k = 0;
+  while (k + 1 < bt.n && int(blockIdx.x) >= bt.chunk0[k + 1]) ++k;
+  const int64_t c0 = int64_t(int(blockIdx.x) - bt.chunk0[k]) * AB_CHUNK, n = bt.count[k];
+  uint32_t key[AB_ITEMS];
+  {
+    int64_t x[AB_ITEMS];
+#pragma unroll
+    for (int r = 0; r < AB_ITEMS; ++r) {
+      const int64_t i = c0 + r * AB_THREADS + threadIdx.x;
+      x[r] = i < n ? ids[bt.begin[k] + i] : int64_t(-1);
+    }
+#pragma unroll
+    for (int r = 0; r < AB_ITEMS; ++r)
+      key[r] = x[r] >= 0 && x[r] < id_bound ? uint32_t(x[r]) : HS_EMPTY;
+  }
+  __syncthreads();
+  // rank[r]: the id's place among its bucket's first occurrences, or EMPTY
+  uint32_t rank[AB_ITEMS];
+#pragma unroll
+  for (int r = 0; r < AB_ITEMS; ++r) {
+    rank[r] = HS_EMPTY;
+    if (key[r] == HS_EMPTY) continue;
+    uint32_t h = (key[r] * 0x9E3779B1u) >> (32 - AB_HASH_BITS);
+    for (;;) {
+      const uint32_t old = s_key[h];
+      if (old == key[r]) break;
+      if (old == HS_EMPTY) {
+        const uint32_t was = atomicCAS(&s_key[h], HS_EMPTY, key[r]);
+        if (was == HS_EMPTY) {
+          rank[r] = atomicAdd(&s_cnt[key[r] >> bits], 1u);
+          break;
+        }
+        if (was == key[r]) break;
+      }
+      h = (h + 1) & ((1u << AB_HASH_BITS) - 1u);
+    }
+  }
+  __syncthreads();
+  // run starts: exclusive prefix over the buckets, 2 per thread
+  constexpr int PER = AB_MAX_BUCKETS / AB_THREADS;
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    c[j] = s_cnt[threadIdx.x * PER + j];
+    sum += c[j];
+  }
+  uint32_t inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o, 64);
+    if (int(threadIdx.x & 63) >= o) inc += y;
+  }
+  if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = inc;
+  __syncthreads();
+  uint32_t run = inc - sum;
+  for (int w = 0; w < int(threadIdx.x >> 6); ++w) run += s_wave[w];
+  uint16_t* __restrict__ row = starts + int64_t(blockIdx.x) * (B + 1);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int b = int(threadIdx.x) * PER + j;
+    s_cnt[b] = run;
+    if (b <= B) row[b] = uint16_t(run);
+    run += c[j];
+  }
+  if (B == AB_MAX_BUCKETS && threadIdx.x == AB_THREADS - 1) row[B] = uint16_t(run);
+  __syncthreads();
+  E* __restrict__ mine = stage + int64_t(blockIdx.x) * AB_CHUNK;
+  const uint32_t low = (1u << bits) - 1u;
+#pragma unroll
+  for (int r = 0; r < AB_ITEMS; ++r)
+    if (rank[r] != HS_EMPTY)
+      mine[s_cnt[key[r] >> bits] + rank[r]] = E((key[r] & low) | (uint32_t(k) << bits));
+}
+
+template <typename E, int BITS>
+__global__ void __launch_bounds__(AB_THREADS) k_ac_bucket(const uint16_t* __restrict__ starts,
+                                                         const E* __restrict__ stage, int nchunks,
+                                                         int B, int32_t* __restrict__ freq) {
+  constexpr int WORDS = (1 << BITS) / 4;
+  __shared__ uint4 s_map4[WORDS / 4];
+  uint32_t* map = reinterpret_cast<uint32_t*>(s_map4);
+  for (int j = threadIdx.x; j < WORDS / 4; j += AB_THREADS) s_map4[j] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  const int b = int(xcd_tile(blockIdx.x, gridDim.x));
+  auto mark = [&](uint32_t e) {
+    const uint32_t id = e & ((1u << BITS) - 1u);
+    atomicOr(&map[id >> 2], 1u << (8 * (id & 3u) + (e >> BITS)));
+  };
+  constexpr int G = 2, J = 8;      // runs of G chunks and J entries of each in flight per thread
+  for (int g0 = threadIdx.x; g0 < nchunks; g0 += G * AB_THREADS) {
+    uint32_t at[G], cnt[G], x[G][J];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const int g = g0 + q * AB_THREADS;
+      const uint16_t* r = starts + int64_t(g) * (B + 1) + b;
+      at[q] = g < nchunks ? r[0] : 0u;
+      cnt[q] = g < nchunks ? uint32_t(r[1]) - at[q] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q)
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (uint32_t(j) < cnt[q]) x[q][j] = stage[int64_t(g0 + q * AB_THREADS) * AB_CHUNK + at[q] + j];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (uint32_t(j) < cnt[q]) mark(x[q][j]);
+      for (uint32_t j = J; j < cnt[q]; ++j)
+        mark(stage[int64_t(g0 + q * AB_THREADS) * AB_CHUNK + at[q] + j]);
+    }
+  }
+  __syncthreads();
+  int32_t* __restrict__ f = freq + (int64_t(b) << BITS);     // only ids below the bound are marked
+  for (int j = threadIdx.x; j < WORDS; j += AB_THREADS) {
+    const uint32_t w = map[j];
+    if (w == 0u) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = __popc((w >> (8 * q)) & 0xffu);
+      // an add without an answer: no thread waits for the counter's line
+      if (c) __hip_atomic_fetch_add(&f[4 * j + q], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// Bucket width for a universe, 0 where there would be too many buckets.
+static int ab_bits(int64_t id_bound) {
+  int bits = AB_MIN_BITS;
+  while (bits < AB_MAX_BITS && ((id_bound - 1) >> bits) + 1 > AB_MAX_BUCKETS) ++bits;
+  return ((id_bound - 1) >> bits) + 1 <= AB_MAX_BUCKETS ? bits : 0;
+}
+
+struct AbPlan {
+  int bits = 0, B = 0, group = 0;    // group: batches per pass
+  size_t stage_off = 0;              // of the stage region, after the run starts
+};
+
+// Batches per pass (at most AC_GROUP) whose stages and run starts fit the
+// workspace whichever batches come together.
+static AbPlan ab_plan(const int64_t* offs, int64_t num_batches, int64_t id_bound, size_t ws_bytes) {
+  AbPlan p;
+  p.bits = ab_bits(id_bound);
+  if (!p.bits) return p;
+  p.B = int(((id_bound - 1) >> p.bits) + 1);
+  int64_t most = 0;
+  for (int64_t k = 0; k < num_batches; ++k) {
+    const int64_t c = (offs[k + 1] - offs[k] + AB_CHUNK - 1) / AB_CHUNK;
+    most = c > most ? c : most;
+  }
+  const size_t esz = p.bits + 3 <= 16 ? 2 : 4;
+  for (int g = AC_GROUP; g >= 1 && most > 0; --g) {
+    const int64_t chunks = most * g;
+    p.stage_off = align_up(size_t(chunks) * size_t(p.B + 1) * 2, 256);
+    if (chunks < (int64_t(1) << 24) && p.stage_off + size_t(chunks) * AB_CHUNK * esz <= ws_bytes) {
+      p.group = g;
+      break;
+    }
+  }
+  return p;
+}
+
+template <typename E>
+static void ab_mark(int bits, int B, int nchunks, const uint16_t* starts, const void* stage,
+                    int32_t* freq, hipStream_t st) {
+#define FAST_AB(BITS_)                                                                             \
+  case BITS_:                                                                                      \
+    hipLaunchKernelGGL((k_ac_bucket<E, BITS_>), dim3(uint32_t(B)), dim3(AB_THREADS), 0, st, starts, \
+                       static_cast<const E*>(stage), nchunks, B, freq);                            \
+    break;
+  if constexpr (sizeof(E) == 2) {
+    switch (bits) { FAST_AB(12) FAST_AB(13) default: break; }
+  } else {
+    switch (bits) { FAST_AB(14) FAST_AB(15) FAST_AB(16) FAST_AB(17) default: break; }
+  }
+#undef FAST_AB
+}
+
+static void ab_count(const AbPlan& p, const int64_t* ids, const int64_t* offs, int64_t num_batches,
+                     int64_t id_bound, int32_t* freq, char* ws, hipStream_t st) {
+  uint16_t* starts = reinterpret_cast<uint16_t*>(ws);
+  char* stage = ws + p.stage_off;
+  for (int64_t g0 = 0; g0 < num_batches; g0 += p.group) {
+    AbBatches bt = {};
+    bt.n = int(num_batches - g0 < p.group ? num_batches - g0 : p.group);
+    int chunks = 0;
+    for (int k = 0; k < bt.n; ++k) {
+      bt.begin[k] = offs[g0 + k];
+      bt.count[k] = offs[g0 + k + 1] - offs[g0 + k];
+      bt.chunk0[k] = chunks;
+      chunks += int((bt.count[k] + AB_CHUNK - 1) / AB_CHUNK);
+    }
+    bt.chunk0[bt.n] = chunks;
+    if (chunks == 0) continue;
+    if (p.bits + 3 <= 16) {
+      hipLaunchKernelGGL(k_ac_stage<uint16_t>, dim3(uint32_t(chunks)), dim3(AB_THREADS), 0, st, ids, bt,
+                         id_bound, p.bits, p.B, starts, reinterpret_cast<uint16_t*>(stage));
+      ab_mark<uint16_t>(p.bits, p.B, chunks, starts, stage, freq, st);
+    } else {
+      hipLaunchKernelGGL(k_ac_stage<uint32_t>, dim3(uint32_t(chunks)), dim3(AB_THREADS), 0, st, ids, bt,
+                         id_bound, p.bits, p.B, starts, reinterpret_cast<uint32_t*>(stage));
+      ab_mark<uint32_t>(p.bits, p.B, chunks, starts, stage, freq, st);
+    }
+  }
+}
+
 static bool use_count_bytemap(int64_t total_ids, int64_t num_batches, int64_t id_bound) {
   static const int mode = [] {
-    const char* e = std::getenv("FAST_COUNT_MARK");   // tuning override: bytemap | stamp
+    const char* e = std::getenv("FAST_COUNT_MARK");   // tuning override: bytemap | stamp | bucket
     if (!e) return 0;
-    return std::strcmp(e, "bytemap") == 0 ? 1 : std::strcmp(e, "stamp") == 0 ? 2 : 0;
+    return std::strcmp(e, "bytemap") == 0 ? 1 : std::strcmp(e, "stamp") == 0 || std::strcmp(e, "bucket") == 0 ? 2 : 0;
   }();
   if (mode) return mode == 1;
   const int64_t mean = num_batches > 0 ? total_ids / num_batches : 0;
   return id_bound <= AC_BYTEMAP_RATIO * (mean > 0 ? mean : 1);
+}
+
+static bool use_count_buckets() {
+  static const bool on = [] {
+    const char* e = std::getenv("FAST_COUNT_MARK");   // the override above: stamp turns them off
+    return !(e && std::strcmp(e, "stamp") == 0);
+  }();
+  return on;
 }
 
 // Masks for up to 32 batches (at most four clears of a byte per id, no
@@ -799,6 +1056,18 @@ extern "C" fast_status_t fast_access_count(const int64_t* ids, const int64_t* ba
       hipLaunchKernelGGL(k_ac_accumulate, dim3(grid_for(n16 * 4, HS_THREADS * 4)), dim3(HS_THREADS), 0,
                          st, reinterpret_cast<const uint32_t*>(map), n16 * 4, np, freq);
     }
+    return check_launch(fn);
+  }
+  // Sparse universes of up to 2^28 ids, where the stages fit the workspace
+  // (the query's size, whatever was passed): 8 batches of 2.64 M Zipf ids of a
+  // 2e8-id universe 729 -> 335 us.  Dense ones stay with the byte maps: the
+  // same batches of a 1e7-id universe 267 us there, 238 this way in two groups,
+  // and their workspace, four bytes per id, often holds no group at all.
+  const AbPlan plan = use_count_buckets() && aligned(ws, 16)
+                          ? ab_plan(batch_offsets, num_batches, id_bound, need)
+                          : AbPlan();
+  if (plan.group > 0) {
+    ab_count(plan, ids, batch_offsets, num_batches, id_bound, freq, static_cast<char*>(ws), st);
     return check_launch(fn);
   }
   if (count_masks(num_batches)) {

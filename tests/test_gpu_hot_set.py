@@ -65,9 +65,8 @@ def _check_slots(slot, hot, n):
 
 @pytest.mark.parametrize("cfg,k", [(2, 12), (3, 4), (1, 6), (2, 40)])
 def test_access_count_and_selection_vs_oracle(cfg, k):
-    """cfg 2's edge ids are counted in the sparse form: 12 batches with batch
-    bits in two groups, 40 batches with stamps; the other universes are dense
-    (a byte map per batch)."""
+    """cfg 2's edge ids are counted in the sparse form (buckets, in two and five
+    groups of batches); the other universes are dense (a byte map per batch)."""
     nodes, edges, nb, eb = presampled_ids(cfg, k)
     _announce(f"hot set cfg={cfg} batches={k} |V|={nb} |E|={eb}")
     fv = _count_gpu(nodes, nb)
@@ -99,6 +98,35 @@ def test_access_count_repeats_invalid_ids_and_accumulation(bound):
                                freq=oracle.access_count(batches, bound))
     assert np.array_equal(f.cpu().numpy(), want)
     assert f[5].item() == 2 and f[3].item() == 2 and f[top].item() == 1
+
+
+@pytest.mark.parametrize("bound,batches,size", [
+    (1000, 12, 10), (1000, 40, 10),              # no room for a stage: masks, stamps
+    (20_000, 40, 100),                           # room for two batches a pass
+    (4096 * 33, 9, 1000), (4096 * 33 + 1, 9, 1000),
+    (1 << 20, 8, 16_384), (1 << 20, 17, 16_385), # whole chunks, one id more
+    (2048 << 13, 3, 50_000), ((2048 << 13) + 1, 3, 50_000),   # 16- and 32-bit entries
+    (1 << 28, 2, 100_000), ((1 << 28) + 1, 2, 100_000),       # the widest buckets, masks beyond
+])
+def test_access_count_sparse_forms(bound, batches, size):
+    """Sparse universes: bucket widths, chunk edges, uneven and empty batches, groups of batches, hot and
+    repeated ids, ids outside the universe; counts added to what freq held."""
+    _announce(f"access count sparse bound={bound} batches={batches} size={size}")
+    r = np.random.default_rng(bound + batches)
+    bs = []
+    for k in range(batches):
+        n = 0 if k == 1 else size if k != 2 else size // 3
+        x = r.integers(-2, bound + 2, n)
+        x[r.random(n) < 0.4] = bound - 1                  # a hot id in every chunk
+        x[r.random(n) < 0.2] = r.integers(0, min(bound, 100))
+        bs.append(x.astype(np.int64))
+    start = torch.full((bound,), 3, dtype=torch.int32, device="cuda")
+    got = _count_gpu(bs, bound, freq=start).cpu().numpy()
+    want = np.full(bound, 3, np.int32)
+    for x in bs:
+        u = np.unique(x)
+        want[u[(u >= 0) & (u < bound)]] += 1
+    assert np.array_equal(got, want)
 
 
 def test_selection_edge_cases():
