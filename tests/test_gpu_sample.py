@@ -97,6 +97,21 @@ def test_sample_recent_random(seed):
     _assert_equal_sample(got, want, f"random seed={seed}")
 
 
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 32_768, 32_769, 131_072, 131_073])
+def test_sample_recent_tile_edges(R):
+    """Root counts around the tiles of 16 and 64 roots and the counts at which the tiles grow and their
+    sums get a scan of their own; lists shorter and longer than a search's 16 probes."""
+    _announce(f"sample recent tile edges R={R}")
+    g = make_temporal_graph(2000, 60_000, seed=77)
+    r = np.random.default_rng(R)
+    roots = r.integers(-1, 2001, R).astype(np.int64)
+    rt = (r.uniform(0, 1.05, R) * float(g.ev_t.max())).astype(np.float32)
+    got = _sample_gpu(DevGraph(g), roots, rt, 5)
+    want = oracle_sample_chunks(g, roots, rt, 5, 8192) if R > 40_000 else \
+        oracle.sample_recent(g.indptr, g.nbr, g.ts, g.eid, roots, rt, 5)
+    _assert_equal_sample(got, want, f"R={R}")
+
+
 def test_two_hops_feed_the_block_operators():
     _announce("sample two hops -> contract check -> time encoding")
     g = make_temporal_graph(50000, 500000, seed=4)
