@@ -6,8 +6,9 @@
 // distinct set is a bitmap over that universe; the rank of an id is the
 // exclusive popcount prefix of the bitmap words below it plus a popcount
 // inside its word.  This is exact and deterministic whatever the id order or
-// thread interleaving, and needs no sort.  The bitmap is built one of three
-// ways, chosen from (n, id_bound) alone:
+// thread interleaving, and needs no sort.  Small batches over small universes
+// take one launch with the bitmap in LDS (k_dedup_small).  Otherwise the bitmap
+// is built one of three ways, chosen from (n, id_bound) alone:
 //   * byte map (id_bound <= 32 n): every id stores 1 into its own byte with a
 //     plain store (racing stores of the same value are benign), then one
 //     pass packs 32 bytes into each bitmap word -- O(n + id_bound) bytes,
@@ -59,7 +60,7 @@ constexpr int MARK_SLOTS = 2 * MARK_IDS;        // load factor <= 1/2: probing a
 static_assert(MARK_SLOTS == 4096, "the hash below yields 12 bits");
 constexpr uint32_t MARK_EMPTY = 0xffffffffu;     // never a word index (W <= 2^30)
 
-enum MarkPath { MARK_BYTES, MARK_BUCKETS, MARK_HASH };
+enum MarkPath { MARK_BYTES, MARK_BUCKETS, MARK_HASH, MARK_LDS };
 
 struct BkPlan {
   int bits = 0;       // 0: no bucketed plan for this universe and batch
@@ -81,13 +82,19 @@ static BkPlan bucket_plan(int64_t n, int64_t id_bound) {
   return p;
 }
 
-static MarkPath mark_path(int64_t n, int64_t id_bound, BkPlan* plan) {
+// Tuning override FAST_DEDUP_MARK: bytemap 1 | hash 2 | bucket 3 (0: none).
+static int mark_override() {
   static const int mode = [] {
-    const char* e = std::getenv("FAST_DEDUP_MARK");   // tuning override: bytemap | bucket | hash
+    const char* e = std::getenv("FAST_DEDUP_MARK");
     if (!e) return 0;
     return std::strcmp(e, "bytemap") == 0 ? 1 : std::strcmp(e, "hash") == 0 ? 2
          : std::strcmp(e, "bucket") == 0 ? 3 : 0;
   }();
+  return mode;
+}
+
+static MarkPath mark_path(int64_t n, int64_t id_bound, BkPlan* plan) {
+  const int mode = mark_override();
   const BkPlan p = bucket_plan(n, id_bound);
   if (plan) *plan = p;
   if (mode == 1) return MARK_BYTES;
@@ -493,6 +500,119 @@ __global__ void __launch_bounds__(DD_THREADS) k_dedup_uni_inv(const uint2* __res
   }
 }
 
+// Small batches over small universes: the whole of steps 1-3 in one launch,
+// the bitmap in LDS.  Every later step of the general paths waits for the
+// launch before it (5 to 6 launches of 2-10 us for a few microseconds of work
+// each).  Here every workgroup marks all n ids in a bitmap of its own (an LDS
+// atomic where the bit is not seen set yet), ranks it by a block scan over
+// groups of DS_GROUP words, and then writes rank, place in uni and slot of
+// its own DS_SLICE ids (copies of one id write the same values, also from
+// several workgroups).  Bound by the latency of marking, so its time grows
+// with n; it ends where the general paths' launches cost as much.
+constexpr int DS_THREADS = 1024;
+constexpr int DS_WAVES = DS_THREADS / 64;
+constexpr int DS_GROUP = 8;                      // words per rank base: two 16-byte LDS reads
+constexpr int DS_UNROLL = 8;                     // ids in flight per thread
+constexpr int DS_SLICE = 2048;                   // ids written per workgroup
+constexpr int64_t DS_MAX_WORDS = 32768;          // 128 KB of LDS: universes of 2^20 ids
+constexpr int64_t DS_MAX_IDS = 32768;
+constexpr int DS_PER = int(DS_MAX_WORDS) / DS_GROUP / DS_THREADS;
+
+// Two calls on n ids each (400- and 688-byte rows), us,
+// general paths / this one: 600 ids 43 / 22, 16,000 uniform ids of 10,000 46 /
+// 22 and of 1e6 57 / 29, 32,000 of 1e6 uniform 52 / 40, Zipf 47 / 29.
+static bool small_batch(int64_t n, int64_t W) {
+  return n > 0 && n <= DS_MAX_IDS && W > 0 && W <= DS_MAX_WORDS && mark_override() == 0;
+}
+
+__global__ void __launch_bounds__(DS_THREADS) k_dedup_small(
+    const int64_t* __restrict__ ids, int n, int64_t id_bound, int W, int64_t* __restrict__ uni,
+    int32_t* __restrict__ inv, int64_t* __restrict__ num_unique, const int32_t* __restrict__ slot_map,
+    int32_t* __restrict__ slots, int64_t* __restrict__ zero_miss) {
+  __shared__ uint4 s_bm4[DS_MAX_WORDS / 4];
+  __shared__ uint32_t s_base[DS_MAX_WORDS / DS_GROUP];
+  __shared__ uint32_t s_wave[DS_WAVES];
+  uint32_t* bm = reinterpret_cast<uint32_t*>(s_bm4);
+  const int groups = (W + DS_GROUP - 1) / DS_GROUP;
+  for (int j = threadIdx.x; j < groups * (DS_GROUP / 4); j += DS_THREADS) s_bm4[j] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  for (int i0 = threadIdx.x; i0 < n; i0 += DS_UNROLL * DS_THREADS) {
+    int64_t x[DS_UNROLL];
+#pragma unroll
+    for (int r = 0; r < DS_UNROLL; ++r) x[r] = i0 + r * DS_THREADS < n ? ids[i0 + r * DS_THREADS] : int64_t(-1);
+#pragma unroll
+    for (int r = 0; r < DS_UNROLL; ++r)
+      if (x[r] >= 0 && x[r] < id_bound) {
+        const uint32_t bit = 1u << (x[r] & 31);
+        if (!(bm[x[r] >> 5] & bit)) atomicOr(&bm[x[r] >> 5], bit);
+      }
+  }
+  __syncthreads();
+  // base ranks: thread t owns groups t DS_PER ...
+  uint32_t c[DS_PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < DS_PER; ++k) {
+    const int gr = int(threadIdx.x) * DS_PER + k;
+    c[k] = 0;
+    if (gr < groups) {
+      const uint4 a = s_bm4[2 * gr], b = s_bm4[2 * gr + 1];
+      c[k] = __popc(a.x) + __popc(a.y) + __popc(a.z) + __popc(a.w) + __popc(b.x) + __popc(b.y) +
+             __popc(b.z) + __popc(b.w);
+    }
+    sum += c[k];
+  }
+  uint32_t inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o, 64);
+    if (int(threadIdx.x & 63) >= o) inc += y;
+  }
+  if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = inc;
+  __syncthreads();
+  uint32_t run = inc - sum;
+  for (int w = 0; w < int(threadIdx.x >> 6); ++w) run += s_wave[w];
+#pragma unroll
+  for (int k = 0; k < DS_PER; ++k) {
+    const int gr = int(threadIdx.x) * DS_PER + k;
+    if (gr < groups) s_base[gr] = run;
+    run += c[k];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == DS_THREADS - 1) {
+    *num_unique = int64_t(run);
+    if (zero_miss) *zero_miss = 0;
+  }
+  __syncthreads();
+  constexpr int U = DS_SLICE / DS_THREADS;
+  const int i0 = int(blockIdx.x) * DS_SLICE + int(threadIdx.x);
+  int64_t x[U];
+  int32_t sl[U];
+#pragma unroll
+  for (int r = 0; r < U; ++r) x[r] = i0 + r * DS_THREADS < n ? ids[i0 + r * DS_THREADS] : int64_t(-1);
+  if (slots) {
+#pragma unroll
+    for (int r = 0; r < U; ++r) sl[r] = x[r] >= 0 && x[r] < id_bound ? slot_map[x[r]] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < U; ++r) {
+    const int i = i0 + r * DS_THREADS;
+    if (i >= n) break;
+    if (x[r] < 0 || x[r] >= id_bound) {
+      inv[i] = -1;
+      continue;
+    }
+    const int w = int(x[r] >> 5), gr = w / DS_GROUP, j = w % DS_GROUP;
+    const uint4 a = s_bm4[2 * gr], b = s_bm4[2 * gr + 1];
+    const uint32_t q[DS_GROUP] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const uint32_t below = (1u << (x[r] & 31)) - 1u;
+    uint32_t k = s_base[gr];
+#pragma unroll
+    for (int t = 0; t < DS_GROUP; ++t) k += __popc(q[t] & (t < j ? 0xffffffffu : t == j ? below : 0u));
+    inv[i] = int32_t(k);
+    uni[k] = x[r];
+    if (slots) slots[k] = sl[r];
+  }
+}
+
 // Row copy: thread t of a block moves vector c of row k; a block covers
 // `rpb` consecutive rows of `cpr` vectors each and strides over row groups,
 // so the grid is sized for the machine, not for the worst-case n.  Rows
@@ -730,13 +850,23 @@ static fast_status_t dedup_gather_run(const char* fn, const int64_t* ids, int64_
   dedup_layout(n, id_bound, static_cast<char*>(ws), &w);
   const int64_t W = (id_bound + 31) / 32;
 
+  // Without a slot map and with a row for every id (id_bound <= table_rows)
+  // nothing can miss: no flags, no scan, and the miss count is 0.
+  const bool all_hit = !slot_map && id_bound <= table_rows;
+  const bool want_miss = (miss || num_miss) && !all_hit;
+  int32_t* slots = slot_map && (rows || want_miss) ? w.slots : nullptr;
+  int64_t* zero_miss = all_hit ? num_miss : nullptr;
+
   BkPlan p;
-  const MarkPath path = mark_path(n, id_bound, &p);
+  const MarkPath path = small_batch(n, W) ? MARK_LDS : mark_path(n, id_bound, &p);
   const uint32_t* base = nullptr;   // bucket base ranks (bucketed marking only)
   const int wshift = path == MARK_BUCKETS ? p.bits - 5 : 0;
   hipError_t e = hipSuccess;
   // 1. mark ids, 2. word ranks (exclusive popcount prefix) and u
-  if (path == MARK_BUCKETS) {
+  if (path == MARK_LDS) {   // ... and 3. uni, inv and slots
+    hipLaunchKernelGGL(k_dedup_small, dim3(uint32_t((n + DS_SLICE - 1) / DS_SLICE)), dim3(DS_THREADS), 0, st, ids, int(n), id_bound, int(W), uni,
+                       inv, num_unique, slot_map, slots, zero_miss);
+  } else if (path == MARK_BUCKETS) {
     const int B = int(p.B), nblk = int(p.nblk);
     if (nblk > 0) {
       hipLaunchKernelGGL(k_bk_stage, dim3(uint32_t(nblk)), dim3(DD_THREADS), 0, st, ids, n, id_bound,
@@ -781,15 +911,11 @@ static fast_status_t dedup_gather_run(const char* fn, const int64_t* ids, int64_
   }
   if (e != hipSuccess) return fail(FAST_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
   // 3. uni and inv (and the slots of the unique ids, when rows or misses
-  // go through a slot map).  Without a slot map and with a row for every id
-  // (id_bound <= table_rows) nothing can miss: no flags, no scan, and the
-  // miss count is 0.
-  const bool all_hit = !slot_map && id_bound <= table_rows;
-  const bool want_miss = (miss || num_miss) && !all_hit;
-  int32_t* slots = slot_map && (rows || want_miss) ? w.slots : nullptr;
+  // go through a slot map)
   const int64_t nbw = (W + DD_THREADS - 1) / DD_THREADS, nbi = (n + DD_THREADS - 1) / DD_THREADS;
-  int64_t* zero_miss = all_hit ? num_miss : nullptr;
-  if (nbw + nbi > 0)
+  if (path == MARK_LDS) {
+    // done
+  } else if (nbw + nbi > 0)
     hipLaunchKernelGGL(k_dedup_uni_inv, dim3(uint32_t(nbw + nbi)), dim3(DD_THREADS), 0, st, w.words, W,
                        base, wshift, uni, ids, n, id_bound, inv, slot_map, slots, uint32_t(nbw),
                        zero_miss);

@@ -51,12 +51,28 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_off_batch_reduce(OffBatch B, u
   if (threadIdx.x == 0) tsum[t] = total;
 }
 
+// Blocks of few tiles: a tile adds up the counts before it itself, and the
+// reduce launch is saved.  At most OFF_ONE_TILES tiles per block: 6 x 2048
+// counts are 48 loads per thread, in flight together.
+constexpr int64_t OFF_ONE_TILES = 7;
+
 __global__ void __launch_bounds__(SCAN_THREADS) k_off_batch_down(OffBatch B, const uint32_t* tsum) {
   __shared__ uint32_t lds4[4];
   const int64_t t = blockIdx.x;
   const int b = batch_block(B, t);
   uint32_t part = 0;
-  for (int64_t j = B.t0[b] + threadIdx.x; j < t; j += SCAN_THREADS) part += tsum[j];
+  if (tsum) {
+    for (int64_t j = B.t0[b] + threadIdx.x; j < t; j += SCAN_THREADS) part += tsum[j];
+  } else {
+    const int32_t* __restrict__ c = B.counts[b] + threadIdx.x;
+    for (int64_t k = 0; k < t - B.t0[b]; ++k) {     // whole tiles
+      int32_t x[SCAN_ITEMS];
+#pragma unroll
+      for (int j = 0; j < SCAN_ITEMS; ++j) x[j] = c[k * SCAN_TILE + j * SCAN_THREADS];
+#pragma unroll
+      for (int j = 0; j < SCAN_ITEMS; ++j) part += uint32_t(x[j]);
+    }
+  }
   uint32_t tile_base;
   block_exclusive_scan(part, lds4, tile_base);   // block-wide sum of the parts
   uint32_t total;
@@ -108,6 +124,21 @@ static bool batch_one_pair(int nblocks, const int64_t* n) {
   return tiles > 0;
 }
 
+// One launch: every block has few tiles, and no offsets overlap counts that
+// another tile may still have to read.
+static bool batch_one_launch(int nblocks, const int32_t* const* counts, const int64_t* n,
+                             int32_t* const* offsets) {
+  for (int b = 0; b < nblocks; ++b) {
+    if (scan_tiles(n[b]) > OFF_ONE_TILES) return false;
+    const uintptr_t c0 = reinterpret_cast<uintptr_t>(counts[b]), c1 = c0 + size_t(n[b]) * 4;
+    for (int k = 0; k < nblocks; ++k) {
+      const uintptr_t o0 = reinterpret_cast<uintptr_t>(offsets[k]), o1 = o0 + size_t(n[k] + 1) * 4;
+      if (c0 < o1 && o0 < c1) return false;
+    }
+  }
+  return true;
+}
+
 extern "C" size_t fast_csr_offsets_batched_workspace(int nblocks, const int64_t* n) {
   if (nblocks < 0 || (nblocks > 0 && !n)) return 0;
   size_t single = 256, tiles = 0;
@@ -157,8 +188,9 @@ extern "C" fast_status_t fast_csr_offsets_batched(int nblocks, const int32_t* co
     t += scan_tiles(n[b]);
   }
   B.t0[nblocks] = t;
-  uint32_t* tsum = static_cast<uint32_t*>(ws);
-  hipLaunchKernelGGL(k_off_batch_reduce, dim3(uint32_t(t)), dim3(SCAN_THREADS), 0, st, B, tsum);
+  uint32_t* tsum = batch_one_launch(nblocks, counts, n, offsets) ? nullptr : static_cast<uint32_t*>(ws);
+  if (tsum)
+    hipLaunchKernelGGL(k_off_batch_reduce, dim3(uint32_t(t)), dim3(SCAN_THREADS), 0, st, B, tsum);
   hipLaunchKernelGGL(k_off_batch_down, dim3(uint32_t(t)), dim3(SCAN_THREADS), 0, st, B,
                      static_cast<const uint32_t*>(tsum));
   return check_launch(fn);

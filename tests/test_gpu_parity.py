@@ -700,6 +700,29 @@ def test_dedup_edge_cases(case):
         assert nm == u and np.array_equal(miss[:nm].cpu().numpy(), np.arange(u))
 
 
+@pytest.mark.parametrize("bound", [1, 31, 256, 257, 40_000, 2**20 - 31, 2**20, 2**20 + 1])
+@pytest.mark.parametrize("n", [1, 2047, 2049, 9000, 32_768, 32_769])
+def test_dedup_small_batches(bound, n):
+    """Both sides of the sizes that one launch with the bitmap in LDS takes (32,768 ids, 2^20 ids of universe),
+    around its slices of 2048 ids and rank groups of 256 ids: hot ids, ids outside the universe, rows
+    by id and through a slot map with misses."""
+    _announce(f"dedup small batch bound={bound} n={n}")
+    r = np.random.default_rng(bound + n)
+    ids = np.where(r.random(n) < 0.3, bound - 1, r.integers(-1, bound + 1, n)).astype(np.int64)
+    valid = (ids >= 0) & (ids < bound)
+    ref_uni, ref_inv = oracle.dedup(ids[valid])
+    sm = np.where(r.random(bound) < 0.5, r.integers(0, 50, bound), -1).astype(np.int32)
+    for slot_map in (None, sm):
+        table = make_table(bound if slot_map is None else 50, 6, "f32", device="cuda", seed=3)
+        uni, inv, u, rows, miss, nm = _dedup(ids, bound, table,
+                                             slot_map=None if slot_map is None else to_dev(slot_map))
+        assert u == ref_uni.size and np.array_equal(uni, ref_uni)
+        assert np.array_equal(inv[valid], ref_inv) and np.all(inv[~valid] == -1)
+        ref_rows, hit, ref_miss = oracle.gather(ref_uni, _bits(table), slot_map)
+        assert nm == ref_miss.size and np.array_equal(miss[:nm].cpu().numpy(), ref_miss)
+        assert np.array_equal(_bits(rows)[hit], ref_rows[hit])
+
+
 @pytest.mark.parametrize("bound,n", [(2**29, 3000), (2**31, 3000), (2**31 + 1, 3000), (2**33 + 5, 50_000),
                                      (3 * 10**7 + 13, 300_000), (40_000, 1200), (2**31, 9_000_000)])
 def test_dedup_sparse_universes(bound, n):
