@@ -20,26 +20,48 @@
 // fmaf(max|omega|, |dt|, max|phi|) exceeds 1e6 (or is not finite) is left
 // to the library sine in a cold second pass of the workgroups that met one.
 //
-// Determinism: the reduction order depends only on N and d_t.  A workgroup
-// owns the segment groups b, b + nblk, b + 2*nblk, ... (TB_SEGS segments
-// each, nblk = min(groups, TB_MAX_BLOCKS)); each thread accumulates its
-// column chunk over its rows in a fixed order, the row lanes are added in
-// lane order through LDS, and a second kernel adds the per-workgroup partials
-// in a fixed tree.  Repeated calls give bitwise-identical results.
+// Determinism: the reduction order depends only on N, E, d_t and
+// the width of a thread's accesses.
+// Workgroup b of nblk = tb_grid(N, E, VEC) owns the b-th of nblk equal ranges of
+// edges; each thread accumulates its column chunk over its rows in a fixed
+// order, the row lanes are added in lane order through LDS, and a second
+// kernel adds the per-workgroup partials in a fixed tree.  Repeated calls give
+// bitwise-identical results.
+//
+// Bound by fp64 issue (about 20 vector instructions per element), so the chip
+// has to stay full to the end: as many workgroups as are resident at once, all
+// with the same number of edges.  Groups of 32 segments dealt out to 2048
+// workgroups left some with five groups and most with four, in two rounds of
+// residence: 2.64 M edges of 264,000 segments x 100 fp32 286 -> 258 us, 0.19 M of
+// ragged ones x 128 bf16 52 -> 41 us.  More rows of dte in flight per thread
+// (2, 4, 5) change nothing or cost registers: 268 / 265 / 263 us.
 #include "common.h"
 
 namespace fast {
 
 constexpr int TB_THREADS = 256;
-constexpr int TB_SEGS = 32;          // destination segments per group
+constexpr int TB_SEGS = 8;           // destination segments per workgroup, on average, up to
+constexpr int TB_MAX_BLOCKS = 1280;  // 5 workgroups per CU, what the registers hold at once
+constexpr int TB_WIN = TB_THREADS;   // segments whose ends and times a tile stages
 constexpr int TB_TILE_MAX = 256;     // rows staged per tile
-constexpr int TB_MAX_BLOCKS = 2048;  // 8 workgroups per CU
 constexpr int TB_MAX_VEC = 8;
 
-__host__ __device__ inline int64_t tb_groups(int64_t N) { return (N + TB_SEGS - 1) / TB_SEGS; }
 __host__ __device__ inline int64_t tb_blocks(int64_t N) {
-  const int64_t g = tb_groups(N);
+  const int64_t g = (N + TB_SEGS - 1) / TB_SEGS;
   return g < TB_MAX_BLOCKS ? g : TB_MAX_BLOCKS;
+}
+// Workgroups of a call.  A workgroup pays for its start and for 2 d_t partials
+// that are written and read again: 128 edges each while the chip is not full
+// (20,000 edges 12 us with 156 workgroups, 18 with 62), 192 beyond or 320 where a
+// thread has 8 columns and twice the sums (0.24 M edges x 100 fp32: 32 us so, 33.5
+// with 320 edges; x 128 bf16: 39 us so, 46 with 192), up to the workgroups
+// resident at once (8 columns per thread: 4 per CU).
+inline int64_t tb_grid(int64_t N, int64_t E, int vec) {
+  const int64_t most = tb_blocks(N), cap = vec >= 8 ? 1024 : TB_MAX_BLOCKS;
+  const int64_t few = (E + 127) / 128 < 512 ? (E + 127) / 128 : 512, many = E / (vec >= 8 ? 320 : 192);
+  int64_t g = few > many ? few : many;
+  g = g < cap ? g : cap;
+  return g < most ? g : most;
 }
 
 // sin(x) in fp64 for an fp32 x with |x| <= 1e6.  k = round(x / pi) comes
@@ -75,7 +97,72 @@ __device__ __forceinline__ bool tb_row_ok(float om_max, float ph_max, float dt) 
 }
 __device__ __attribute__((noinline)) double sin_library(double x) { return sin(x); }
 
-// Grid: tb_blocks(N) workgroups.  Thread t owns the column chunk t % cpr of
+// Last segment that begins at or before edge e (64 probes at a time; every
+// lane of the wave takes part and returns it); in [0, N) whatever off holds.
+__device__ __forceinline__ int64_t tb_segment(const int32_t* __restrict__ off, int64_t N, int64_t e) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = N;                      // offsets before lo are at most e, from hi on above
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) >> 6;
+    const int64_t p = lo + int64_t(lane + 1) * step - 1;
+    const bool below = p < hi && int64_t(off[p]) <= e;
+    const int c = __popcll(__ballot(below));
+    const int64_t cap = lo + int64_t(c + 1) * step - 1;
+    lo += int64_t(c) * step;
+    hi = cap < hi ? cap : hi;
+  }
+  return lo > 0 ? lo - 1 : 0;
+}
+
+struct TbTile {
+  int32_t end[TB_WIN];                         // of the window's segments
+  float tdst[TB_WIN], dt[TB_TILE_MAX];
+  int next;                                    // the last row's segment in the window
+};
+
+// Calls f(t0, nrows) for tiles of up to `tile` rows that cover the edges
+// [t0, t1), with the rows' time differences in s.dt.  Every thread of the
+// workgroup calls it.  A step consumes rows or a whole window of segments.
+template <class F>
+__device__ __forceinline__ void tb_tiles(TbTile& s, const int32_t* __restrict__ off, int64_t N, int64_t E,
+                                         const float* __restrict__ dst_t, const float* __restrict__ edge_t,
+                                         int64_t t0, int64_t t1, int tile, F&& f) {
+  if (t0 >= t1) return;
+  int64_t seg = tb_segment(off, N, t0);
+  while (t0 < t1) {
+    const int ns = int(N - seg < TB_WIN ? N - seg : TB_WIN);
+    const int64_t e = t0 + threadIdx.x;
+    const float te = int(threadIdx.x) < tile && e < t1 ? edge_t[e] : 0.f;
+    if (int(threadIdx.x) < ns) {
+      s.end[threadIdx.x] = int32_t(clamp64(off[seg + threadIdx.x + 1], 0, E));
+      s.tdst[threadIdx.x] = dst_t[seg + threadIdx.x];
+    }
+    __syncthreads();
+    // rows behind the last segment's end, if any, belong to it
+    const int64_t w1 = seg + ns == N || s.end[ns - 1] > t1 ? t1 : s.end[ns - 1];
+    const int nrows = int(w1 - t0 < tile ? w1 - t0 : tile);
+    if (nrows > 0) {
+      if (int(threadIdx.x) < nrows) {
+        int lo = 0, hi = ns - 1;               // first segment of the window that ends behind e
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (s.end[mid] > e) hi = mid; else lo = mid + 1;
+        }
+        s.dt[threadIdx.x] = s.tdst[lo] - te;
+        if (int(threadIdx.x) == nrows - 1) s.next = lo;
+      }
+      __syncthreads();
+      f(t0, nrows);
+      t0 += nrows;
+      seg += s.next;
+    } else {
+      seg += ns;                               // seg + ns < N: only empty segments in the window
+    }
+    __syncthreads();
+  }
+}
+
+// Grid: tb_grid(N, E, VEC) workgroups.  Thread t owns the column chunk t % cpr of
 // the rows t / cpr, t / cpr + rpp, ... of every tile, as in the forward.
 // partial: [2 * d_t][nblk] fp64 (domega rows first, then dphi).
 template <typename TG, int VEC, bool NT>
@@ -84,12 +171,10 @@ __global__ void __launch_bounds__(TB_THREADS) k_time_encode_bwd(
     const float* __restrict__ edge_t, const float* __restrict__ omega,
     const float* __restrict__ phi, int d_t, const TG* __restrict__ dte,
     double* __restrict__ partial) {
-  __shared__ int64_t s_off[TB_SEGS + 1];
-  __shared__ float s_tdst[TB_SEGS];
-  __shared__ float s_dt[TB_TILE_MAX];
+  __shared__ TbTile s_tile;
   __shared__ double s_red[TB_THREADS * VEC * 2];
 
-  const int64_t ngroups = tb_groups(N), nblk = tb_blocks(N);
+  const int64_t nblk = gridDim.x;
   const int cpr = d_t / VEC;               // vector chunks per row (<= TB_THREADS)
   const int rpp = TB_THREADS / cpr;        // rows per pass
   const int rsub = int(threadIdx.x) / cpr;
@@ -110,92 +195,54 @@ __global__ void __launch_bounds__(TB_THREADS) k_time_encode_bwd(
     acc_p[k] = 0.0;
   }
 
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += nblk) {
-    const int64_t s0 = grp * TB_SEGS;
-    const int ns = int(N - s0 < TB_SEGS ? N - s0 : TB_SEGS);
-    if (threadIdx.x <= ns) s_off[threadIdx.x] = clamp64(off[s0 + threadIdx.x], 0, E);
-    if (threadIdx.x < ns) s_tdst[threadIdx.x] = dst_t[s0 + threadIdx.x];
-    __syncthreads();
-    const int64_t r0 = s_off[0], r1 = s_off[ns] > r0 ? s_off[ns] : r0;
-    for (int64_t t0 = r0; t0 < r1; t0 += tile) {
-      const int nrows = int(r1 - t0 < tile ? r1 - t0 : tile);
-      if (threadIdx.x < nrows) {
-        const int64_t e = t0 + threadIdx.x;
-        int lo = 0, hi = ns - 1;           // last local segment with s_off <= e
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_off[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        s_dt[threadIdx.x] = s_tdst[lo] - edge_t[e];
+  const int64_t e0 = clamp64(off[0], 0, E), e1 = clamp64(off[N], e0, E);
+  const int64_t t0 = e0 + (e1 - e0) * int64_t(blockIdx.x) / nblk;
+  const int64_t t1 = e0 + (e1 - e0) * (int64_t(blockIdx.x) + 1) / nblk;
+  const float* s_dt = s_tile.dt;
+  tb_tiles(s_tile, off, N, E, dst_t, edge_t, t0, t1, tile, [&](int64_t r0, int nrows) {
+    if (!active) return;
+    for (int row = rsub; row < nrows; row += rpp) {
+      const float dt = s_dt[row];
+      if (__builtin_expect(!tb_row_ok(om_max, ph_max, dt), 0)) {
+        big = true;                        // left to the cold pass
+        continue;
       }
-      __syncthreads();
-      if (active) {
-        for (int row = rsub; row < nrows; row += rpp) {
-          const float dt = s_dt[row];
-          if (__builtin_expect(!tb_row_ok(om_max, ph_max, dt), 0)) {
-            big = true;                    // left to the cold pass
-            continue;
-          }
-          Raw<TG, VEC> raw;
-          raw.template load<NT>(dte + (t0 + row) * d_t + c0 * VEC);
-          float g[VEC];
-          raw.unpack(g);
-          const double dtd = double(dt);
+      Raw<TG, VEC> raw;
+      raw.template load<NT>(dte + (r0 + row) * d_t + c0 * VEC);
+      float g[VEC];
+      raw.unpack(g);
+      const double dtd = double(dt);
 #pragma unroll
-          for (int k = 0; k < VEC; ++k) {
-            // the term is -g sin x
-            const double q = double(g[k]) * sin_reduced(fmaf(om[k], dt, ph[k]));
-            acc_p[k] -= q;
-            acc_w[k] = fma(-q, dtd, acc_w[k]);
-          }
-        }
+      for (int k = 0; k < VEC; ++k) {
+        // the term is -g sin x
+        const double q = double(g[k]) * sin_reduced(fmaf(om[k], dt, ph[k]));
+        acc_p[k] -= q;
+        acc_w[k] = fma(-q, dtd, acc_w[k]);
       }
-      __syncthreads();
     }
-  }
+  });
 
   // Cold pass, only in a workgroup that met a row beyond the reduction's
   // range (or not finite): the same rows again, adding just those rows with
   // the library sine.  The order stays a fixed function of the inputs.
   if (__syncthreads_or(big)) {
-    for (int64_t grp = blockIdx.x; grp < ngroups; grp += nblk) {
-      const int64_t s0 = grp * TB_SEGS;
-      const int ns = int(N - s0 < TB_SEGS ? N - s0 : TB_SEGS);
-      if (threadIdx.x <= ns) s_off[threadIdx.x] = clamp64(off[s0 + threadIdx.x], 0, E);
-      if (threadIdx.x < ns) s_tdst[threadIdx.x] = dst_t[s0 + threadIdx.x];
-      __syncthreads();
-      const int64_t r0 = s_off[0], r1 = s_off[ns] > r0 ? s_off[ns] : r0;
-      for (int64_t t0 = r0; t0 < r1; t0 += tile) {
-        const int nrows = int(r1 - t0 < tile ? r1 - t0 : tile);
-        if (threadIdx.x < nrows) {
-          const int64_t e = t0 + threadIdx.x;
-          int lo = 0, hi = ns - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= e) lo = mid; else hi = mid - 1;
-          }
-          s_dt[threadIdx.x] = s_tdst[lo] - edge_t[e];
+    tb_tiles(s_tile, off, N, E, dst_t, edge_t, t0, t1, tile, [&](int64_t r0, int nrows) {
+      if (!active || !big) return;
+      for (int row = rsub; row < nrows; row += rpp) {
+        const float dt = s_dt[row];
+        if (tb_row_ok(om_max, ph_max, dt)) continue;
+        Raw<TG, VEC> raw;
+        raw.template load<false>(dte + (r0 + row) * d_t + c0 * VEC);
+        float g[VEC];
+        raw.unpack(g);
+        for (int k = 0; k < VEC; ++k) {
+          const float x = fmaf(om[k], dt, ph[k]);
+          const double gs = -double(g[k]) * sin_library(double(x));
+          acc_p[k] += gs;
+          acc_w[k] = fma(gs, double(dt), acc_w[k]);
         }
-        __syncthreads();
-        if (active && big) {
-          for (int row = rsub; row < nrows; row += rpp) {
-            const float dt = s_dt[row];
-            if (tb_row_ok(om_max, ph_max, dt)) continue;
-            Raw<TG, VEC> raw;
-            raw.template load<false>(dte + (t0 + row) * d_t + c0 * VEC);
-            float g[VEC];
-            raw.unpack(g);
-            for (int k = 0; k < VEC; ++k) {
-              const float x = fmaf(om[k], dt, ph[k]);
-              const double gs = -double(g[k]) * sin_library(double(x));
-              acc_p[k] += gs;
-              acc_w[k] = fma(gs, double(dt), acc_w[k]);
-            }
-          }
-        }
-        __syncthreads();
       }
-    }
+    });
   }
 
   // row lanes of one column chunk, added in lane order
@@ -242,7 +289,7 @@ __global__ void __launch_bounds__(TB_THREADS) k_time_encode_bwd_final(
 template <typename TG, int VEC>
 static void launch_tb(const fast_tcsr_t* g, const float* omega, const float* phi, int d_t,
                       const void* dte, double* partial, hipStream_t st) {
-  const int64_t nb = tb_blocks(g->num_dst);
+  const int64_t nb = tb_grid(g->num_dst, g->num_edges, VEC);
   const bool nt = (size_t(d_t) * sizeof(TG)) % CACHE_LINE == 0 && aligned(dte, CACHE_LINE);
   if (nt)
     hipLaunchKernelGGL((k_time_encode_bwd<TG, VEC, true>), dim3(uint32_t(nb)), dim3(TB_THREADS),
@@ -307,7 +354,7 @@ extern "C" fast_status_t fast_time_encode_bwd(const fast_tcsr_t* g, const float*
   double* partial = static_cast<double*>(ws);
   int64_t nblk = 0;
   if (g->num_edges > 0) {
-    nblk = tb_blocks(g->num_dst);
+    nblk = tb_grid(g->num_dst, g->num_edges, vec);
     if (dte_dtype == FAST_F32) {
       switch (vec) {
         case 4: launch_tb<float, 4>(g, omega, phi, d_t, dte, partial, st); break;

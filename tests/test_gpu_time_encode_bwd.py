@@ -104,6 +104,23 @@ def test_time_encode_bwd_shapes(d_t, dt):
     assert_close(got[1], ref[1], "f32", f"dphi d_t={d_t}")
 
 
+@pytest.mark.parametrize("counts", [
+    [1], [0] * 700 + [127] + [0] * 700, [128] + [0] * 9, [0] * 9 + [129], [1] * 257, [0, 1] * 300,
+    ([0] * 255 + [2]) * 4 + [3000] + [0] * 256 + [5], [7] * 20011], ids=lambda c: f"N{len(c)}E{sum(c)}")
+def test_time_encode_bwd_edge_ranges(counts):
+    """Equal edge ranges per workgroup: one workgroup and many, ranges that begin inside a hub, runs
+    of empty segments longer than the window of segments that a tile stages."""
+    _announce(f"time encode bwd N={len(counts)} E={sum(counts)}")
+    blk = tiny_graph(counts, seed=len(counts))
+    off = oracle.csr_offsets(blk.counts)
+    om, ph = omega_phi(12)
+    dte = _randn((blk.num_edges, 12), "f32", "cuda", 5)
+    got = _tb_gpu(off, blk.dst_t, blk.edge_t, om, ph, dte)
+    ref = oracle.time_encode_bwd(off, blk.dst_t, blk.edge_t, om, ph, dte.double().cpu().numpy())
+    assert_close(got[0], ref[0], "f32", "domega")
+    assert_close(got[1], ref[1], "f32", "dphi")
+
+
 def test_time_encode_bwd_no_edges_writes_zeros():
     _announce("time encode bwd without edges")
     off = np.zeros(6, np.int32)
