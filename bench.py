@@ -504,7 +504,7 @@ def sampler_ops(b, torch, fast, num_events=20_000_000, reps=5, with_oracle=False
         res[f"sample_recent_hop{hop}"] = {
             "ms": round(ms, 4), "roots": R, "k": k, "sampled_edges": E,
             "graph": f"{g.num_nodes} nodes, {num_events} events ({int(g.indptr[-1])} entries)",
-            "bound": "latency (binary search per root over its time-sorted entries)",
+            "bound": "latency (a search per root over its time-sorted entries)",
             "sampled_edges_per_s": round(E / (ms * 1e-3), 1),
         }
         q_roots, q_t = src[:E].clone(), et[:E].clone()
@@ -558,7 +558,7 @@ def hot_set_ops(b, torch, fast, num_batches=8, alpha=0.01, reps=3, with_oracle=F
         n = int(ids.numel())
         res[f"access_count_{kind}"] = {
             "ms": round(ms, 4), "ids": n, "id_bound": bound, "batches": num_batches,
-            "bound": "random 4-byte atomics (one mask OR per id, one add per distinct id and batch)",
+            "bound": "marks of ids: byte maps in memory (dense universes) or buckets in LDS (sparse ones)",
             "ids_per_s": round(n / (ms * 1e-3), 1),
         }
         if with_oracle:
