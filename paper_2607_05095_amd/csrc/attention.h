@@ -18,7 +18,10 @@
 //     chunk) in base 2, so any degree works and a segment is streamed once.
 //     The loads of a chunk are issued back to back.  A slot that no segment
 //     of the wave needs is skipped by a uniform branch; otherwise slots past
-//     a segment's end re-read its last row (a cache hit) and are masked out.
+//     a segment's end re-read its last row (a cache hit) and are masked out:
+//     they add nothing, whatever the row holds (a weight of 0 alone would turn
+//     an infinite value into NaN, depending on the slots of the segments that
+//     happen to share the wave).
 //     Re-reading alone costs requests on short segments, and a load per
 //     segment under its own mask breaks up the batch of loads.  Re-read /
 //     masked / skipped, layer of 100,000 segments, us: forward of ragged
@@ -334,10 +337,12 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd(AttnArg
       Z += w;
       float vx[P][VE];
       unpack_row<T, VE, P>(vr[i], vx);
+      if (base + i < e1) {
 #pragma unroll
-      for (int p = 0; p < P; ++p)
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(w, vx[p][j], acc[p][j]);
+          for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(w, vx[p][j], acc[p][j]);
+      }
     }
     mx = mn;
   }
@@ -392,7 +397,8 @@ __device__ __forceinline__ void bwd_chunk(const AttnArgs& a, const LaneMap<P>& m
     unpack_row<T, VE, P>(kr[i], kx);
     unpack_row<T, VE, P>(vr[i], vx);
     x[i] = head_dot<VE, P, LPH_CT>(S.q, kx, m.lph) * sl2;
-    da[i] = head_dot<VE, P, LPH_CT>(S.go, vx, m.lph);
+    const float dai = head_dot<VE, P, LPH_CT>(S.go, vx, m.lph);
+    da[i] = base + i < e1 ? dai : 0.f;
     t[i] = base + i < e1 ? lrelu(x[i], a.slope) : -INFINITY;
     cm = fmaxf(cm, t[i]);
   }
@@ -742,10 +748,12 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_fwd(AttnArgs a) {
       float vx[P][VE];
       unpack_row<T, VE, P>(vr[i], vx);
       const float w = al.get(i);
+      if (base + i < e1) {
 #pragma unroll
-      for (int p = 0; p < P; ++p)
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(w, vx[p][j], acc[p][j]);
+          for (int j = 0; j < VE; ++j) acc[p][j] = fmaf(w, vx[p][j], acc[p][j]);
+      }
     }
   }
   store_row<T, VE, P>(static_cast<T*>(a.out), m.seg, F, m, acc);

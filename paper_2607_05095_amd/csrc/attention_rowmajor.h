@@ -177,8 +177,10 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd_rm(Attn
         w[h] = exp2_hw(t[i][h] - mx[h]);
         Z[h] += w[h];
       }
+      if (base + i < e1) {                               // a masked slot's row may be infinite
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = fmaf(pick<H>(w, m.hs[k]), vx[i][k], acc[k]);
+        for (int k = 0; k < 4; ++k) acc[k] = fmaf(pick<H>(w, m.hs[k]), vx[i][k], acc[k]);
+      }
     }
   }
   float inv[H];
@@ -233,6 +235,7 @@ __device__ __forceinline__ void rm_bwd_chunk(const AttnArgs& a, const RmMap<H>& 
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       x[i][h] = d[h] * sl2;
+      da[i][h] = base + i < e1 ? da[i][h] : 0.f;
       t[i][h] = base + i < e1 ? lrelu(x[i][h], a.slope) : -INFINITY;
       cm[h] = fmaxf(cm[h], t[i][h]);
     }

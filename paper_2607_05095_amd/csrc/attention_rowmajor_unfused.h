@@ -241,8 +241,10 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_fwd_rm(AttnArgs a) {
       float w[H];
 #pragma unroll
       for (int h = 0; h < H; ++h) w[h] = al.get(i * H + h);
+      if (base + i < e1) {                               // a masked slot's row may be infinite
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = fmaf(pick<H>(w, m.hs[k]), vx[i][k], acc[k]);
+        for (int k = 0; k < 4; ++k) acc[k] = fmaf(pick<H>(w, m.hs[k]), vx[i][k], acc[k]);
+      }
     }
   }
   rm_store_row<true, H>(static_cast<float*>(a.out), m.seg, F, m, acc);

@@ -230,6 +230,56 @@ def test_attention_chunk_edges(H, dh, dt):
     _check_block(_synthetic_block(counts, H, dh, dt, seed=dh), None, f"chunk edges {H}x{dh} {dt}")
 
 
+def _all_attention_results(d):
+    """Every result of every attention entry point on block d, as fp64 on the host."""
+    o, tt, dt = d.ops, tdtype(d.dt), DT[d.dt]
+    ident = torch.arange(d.E, dtype=torch.int32, device="cuda")
+    res = dict(zip(("out", "lse", "dQ", "dK", "dV"), _run_fused(d)))
+    res.update(zip(("p_out", "p_lse", "p_dQ", "p_dK", "p_dV"), _run_fused_packed(d, with_lse=False)))
+    res.update(zip(("s_alpha", "s_lse", "s_out", "s_dalpha", "s_dV", "s_dQ", "s_dK"), _run_unfused(d)))
+    out, lse, dQ, dK, dV, dQc = d.empty(d.N), d.scalars(d.N), d.empty(d.N), d.empty(d.E), d.empty(d.E), d.empty(d.N)
+    ge, ae = d.scalars(d.E), d.scalars(d.E)
+    ops = (o["Q"], o["K"], ident, d.E, o["V"], ident, d.E, d.scale, SLOPE)
+    fast.fast_edge_attention_fwd_indexed(d.g, d.H, d.dh, dt, *ops, out, lse)
+    fast.fast_edge_attention_bwd_indexed(d.g, d.H, d.dh, dt, *ops, lse, o["dO"], dQ, dK, dV)
+    fast.fast_edge_attention_bwd_indexed_coef(d.g, d.H, d.dh, dt, *ops, lse, o["dO"], dQc, ge, ae)
+    res.update(i_out=out, i_lse=lse, i_dQ=dQ, i_dK=dK, i_dV=dV, c_dQ=dQc, c_g=ge, c_alpha=ae)
+    return {k: _host(v) for k, v in res.items()}
+
+
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (2, 30, "f32"), (4, 32, "f32"), (2, 64, "bf16"), (3, 13, "f32"),
+                                     (2, 50, "bf16"), (2, 14, "f32")])
+def test_attention_infinite_values_stay_in_their_segment(H, dh, dt):
+    """Infinite entries in the value row that a segment's spare chunk slots hold (its last one) and in dOut
+    rows: out is that of the definition (infinite, not 0 x infinity), and every result of a segment
+    is the same whichever segments share its wave, finite or not."""
+    _announce(f"attention infinite values {H}x{dh} {dt}")
+    counts = [3, 10, 1, 7, 2, 0, 13, 4, 5, 1, 10, 2, 24, 26, 3, 1, 0, 6]
+    d = _synthetic_block(counts, H, dh, dt, seed=5)
+    last = [int(d.off[v + 1]) - 1 for v in range(d.N) if counts[v]]
+    for j, e in enumerate(last):
+        if j % 4 != 3:
+            d.ops["V"][e, :, j % dh] = float("inf") if j % 2 else float("-inf")
+    d.ops["dO"][4, 0, 1] = float("inf")
+    got = _all_attention_results(d)
+    tol = 1e-5 if dt == "f32" else 2e-2        # fp32 sums in another order; bf16 results one rounding apart
+    V = _host(d.ops["V"])
+    for v in range(d.N):
+        e0, e1 = int(d.off[v]), int(d.off[v + 1])
+        want = (got["s_alpha"][e0:e1, :, None] * V[e0:e1]).sum(0)
+        for k in ("out", "p_out", "s_out", "i_out"):
+            np.testing.assert_allclose(got[k][v], want, rtol=tol, atol=tol, err_msg=f"{k} of segment {v}")
+        ops = dict(Q=d.ops["Q"][v:v + 1].contiguous(), dO=d.ops["dO"][v:v + 1].contiguous(),
+                   K=d.ops["K"][e0:e1].contiguous(), V=d.ops["V"][e0:e1].contiguous())
+        if e0 == e1:
+            continue
+        alone = _all_attention_results(DevBlock([e1 - e0], d.d_dst_t[v:v + 1].cpu().numpy(),
+                                                d.d_edge_t[e0:e1].cpu().numpy(), ops, H, dh, dt))
+        for k, x in alone.items():
+            r = got[k][v:v + 1] if got[k].shape[0] == d.N else got[k][e0:e1]
+            np.testing.assert_allclose(r, x, rtol=tol, atol=tol, err_msg=f"{k} of segment {v} alone")
+
+
 @pytest.mark.parametrize("slope", [-0.3, 0.0])
 @pytest.mark.parametrize("name,counts,H,dh,dt", [
     ("rowmajor_f32", [10, 1, 0, 7, 30, 10, 25, 3, 12], 2, 50, "f32"),
