@@ -93,19 +93,19 @@ __global__ void __launch_bounds__(ROOTS * L) k_sample_count(
   }
 }
 
-// Offsets and neighbours of one tile.
+// Offsets and neighbours of one tile.  off[i] holds root i's count on entry:
+// only the root's own tile reads it, and writes the offset in its place.
 template <int ROOTS>
 __global__ void __launch_bounds__(ROOTS * SR_GROUP) k_sample_fill(
     const int64_t* __restrict__ nbr, const float* __restrict__ ts,
-    const int64_t* __restrict__ eid, const int32_t* __restrict__ count,
-    const int64_t* __restrict__ start, const uint32_t* __restrict__ tsum, int64_t R,
-    int32_t* __restrict__ off, int64_t* __restrict__ src_ids, float* __restrict__ edge_t,
-    int64_t* __restrict__ edge_ids) {
+    const int64_t* __restrict__ eid, const int64_t* __restrict__ start,
+    const uint32_t* __restrict__ tsum, int64_t R, int32_t* __restrict__ off,
+    int64_t* __restrict__ src_ids, float* __restrict__ edge_t, int64_t* __restrict__ edge_ids) {
   constexpr int THREADS = ROOTS * SR_GROUP;
   __shared__ uint32_t s_part[THREADS / 64], s_off[ROOTS];
   const int sub = int(threadIdx.x) / SR_GROUP, lane = int(threadIdx.x) % SR_GROUP;
   const int64_t r0 = int64_t(blockIdx.x) * ROOTS, i = r0 + sub;
-  const int32_t c = i < R ? count[i] : 0;
+  const int32_t c = i < R ? off[i] : 0;
   const int64_t s = i < R ? start[i] : 0;
   uint32_t before = 0;
   for (int j = threadIdx.x; j < int(blockIdx.x); j += THREADS) before += tsum[j];
@@ -171,9 +171,9 @@ __global__ void __launch_bounds__(SR_THREADS) k_sample_copy(
 }
 
 struct SrWs {
-  int32_t* count;
+  int32_t* count;      // or the tile sums, where the counts lie in dst_offsets
   int64_t* start;
-  uint32_t* tsum;      // tile sums, or the scan's workspace
+  void* scan;
 };
 
 static size_t sr_layout(int64_t R, char* base, SrWs* ws) {
@@ -185,11 +185,11 @@ static size_t sr_layout(int64_t R, char* base, SrWs* ws) {
   };
   char* c = take(size_t(R) * 4);
   char* s = take(size_t(R) * 8);
-  char* sc = take(R <= SR_TILED ? size_t(SR_MAX_TILES) * 4 : scan_workspace(R));
+  char* sc = take(scan_workspace(R));
   if (ws) {
     ws->count = reinterpret_cast<int32_t*>(c);
     ws->start = reinterpret_cast<int64_t*>(s);
-    ws->tsum = reinterpret_cast<uint32_t*>(sc);
+    ws->scan = sc;
   }
   return off;
 }
@@ -233,15 +233,21 @@ extern "C" fast_status_t fast_sample_recent(const fast_temporal_graph_t* g, cons
   sr_layout(num_roots, static_cast<char*>(ws), &w);
   const int64_t R = num_roots;
   const int kk = (g->num_nodes > 0 && g->num_entries > 0) ? k : 0;   // no entries: all empty
+  // tiled: the counts go to dst_offsets and the tile sums (at most R) to their
+  // place in the workspace, which a smaller batch never needs more of than a
+  // larger one
+  const bool tiled = R <= SR_TILED;
+  int32_t* counts = tiled ? dst_offsets : w.count;
+  uint32_t* tsum = tiled ? reinterpret_cast<uint32_t*>(w.count) : nullptr;
   const auto count = [&](auto kernel, int64_t roots_per_wg, int lanes) {
     hipLaunchKernelGGL(kernel, dim3(uint32_t((R + roots_per_wg - 1) / roots_per_wg)),
                        dim3(uint32_t(roots_per_wg * lanes)), 0, st, g->indptr, g->num_nodes,
-                       g->num_entries, g->ts, roots, root_t, R, kk, w.count, w.start, w.tsum);
+                       g->num_entries, g->ts, roots, root_t, R, kk, counts, w.start, tsum);
   };
   const auto fill = [&](auto kernel, int64_t roots_per_wg) {
     hipLaunchKernelGGL(kernel, dim3(uint32_t((R + roots_per_wg - 1) / roots_per_wg)),
-                       dim3(uint32_t(roots_per_wg * SR_GROUP)), 0, st, g->nbr, g->ts, g->eid, w.count,
-                       w.start, w.tsum, R, dst_offsets, src_ids, edge_t, edge_ids);
+                       dim3(uint32_t(roots_per_wg * SR_GROUP)), 0, st, g->nbr, g->ts, g->eid, w.start, tsum,
+                       R, dst_offsets, src_ids, edge_t, edge_ids);
   };
   if (R > 0 && R <= SR_MAX_TILES * SR_SMALL) {
     if (R <= SR_WIDE_SEARCH) count(k_sample_count<SR_SMALL, 16>, SR_SMALL, 16);
@@ -251,12 +257,8 @@ extern "C" fast_status_t fast_sample_recent(const fast_temporal_graph_t* g, cons
     count(k_sample_count<SR_LARGE, 4>, SR_LARGE, 4);
     fill(k_sample_fill<SR_LARGE>, SR_LARGE);
   } else {
-    if (R > 0) {   // a thread per search, no tile sums
-      w.tsum = nullptr;
-      count(k_sample_count<SR_THREADS, 1>, SR_THREADS, 1);
-      sr_layout(R, static_cast<char*>(ws), &w);
-    }
-    const hipError_t e = scan_launch(InRootCount{w.count}, OutRootOffset{dst_offsets}, R, w.tsum, nullptr,
+    if (R > 0) count(k_sample_count<SR_THREADS, 1>, SR_THREADS, 1);   // a thread per search, no tile sums
+    const hipError_t e = scan_launch(InRootCount{w.count}, OutRootOffset{dst_offsets}, R, w.scan, nullptr,
                                      dst_offsets + R, st);
     if (e != hipSuccess) return fail(FAST_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
     if (R > 0 && kk > 0)

@@ -376,6 +376,28 @@ def test_sample_recent_validation():
     assert call(g=ctypes.byref(bad)) == INVALID
 
 
+def test_workspace_of_a_larger_call_serves_smaller_ones():
+    """A program sizes its workspaces once, for its largest batch: no query asks for less at a larger size."""
+    L = fast.lib()
+    sizes = sorted({max(0, b + d) for p in range(26) for b in (2 ** p, 3 * 2 ** p, 2000 * p) for d in (-1, 0, 1, 17)})
+    queries = {
+        "csr_offsets": L.fast_csr_offsets_workspace,
+        "csr_offsets_batched": lambda n: L.fast_csr_offsets_batched_workspace(2, (ctypes.c_int64 * 2)(n, 300)),
+        "sample_recent": L.fast_sample_recent_workspace,
+        "dedup ids": lambda n: L.fast_dedup_gather_workspace(n, 10 ** 6),
+        "access_count": L.fast_access_count_workspace,
+        "hot_set": lambda n: L.fast_greedy_hot_set_workspace(n, 1000, 64),
+        "time_encode_bwd": lambda n: L.fast_time_encode_bwd_workspace(n, 100),
+        "occurrence_csr": lambda n: L.fast_occurrence_csr_workspace(n, 1000),
+        "index_add": lambda n: L.fast_index_add_rows_workspace(n, 1000, 100),
+        "index_add_scaled": lambda n: L.fast_index_add_scaled_rows_workspace(n, 1000, 2, 50),
+    }
+    for name, q in queries.items():
+        got = [q(n) for n in sizes]
+        drops = [(a, b) for a, b, x, y in zip(sizes, sizes[1:], got, got[1:]) if y < x]
+        assert not drops, (name, drops)
+
+
 def test_indexed_operands_validation():
     L = fast.lib()
     gp = ctypes.byref(_g())
