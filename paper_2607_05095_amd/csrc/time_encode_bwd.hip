@@ -117,12 +117,17 @@ __device__ __forceinline__ int64_t tb_segment(const int32_t* __restrict__ off, i
 struct TbTile {
   int32_t end[TB_WIN];                         // of the window's segments
   float tdst[TB_WIN], dt[TB_TILE_MAX];
-  int next;                                    // the last row's segment in the window
+  int64_t next;                                // the last row's segment, from the window's first
 };
 
 // Calls f(t0, nrows) for tiles of up to `tile` rows that cover the edges
 // [t0, t1), with the rows' time differences in s.dt.  Every thread of the
-// workgroup calls it.  A step consumes rows or a whole window of segments.
+// workgroup calls it.  A tile's rows find their segments in a window of TB_WIN
+// segments in LDS, and the tile ends with the window -- unless that leaves less
+// than a quarter of it, as in blocks of mostly empty segments: then each row
+// searches the offsets in memory by itself, and empty segments cost nothing
+// (1000 edges x 100 fp32 of 1e6 segments: 320 us with the windows walked one
+// after the other, 15 so; no difference in dense blocks).
 template <class F>
 __device__ __forceinline__ void tb_tiles(TbTile& s, const int32_t* __restrict__ off, int64_t N, int64_t E,
                                          const float* __restrict__ dst_t, const float* __restrict__ edge_t,
@@ -140,8 +145,8 @@ __device__ __forceinline__ void tb_tiles(TbTile& s, const int32_t* __restrict__ 
     __syncthreads();
     // rows behind the last segment's end, if any, belong to it
     const int64_t w1 = seg + ns == N || s.end[ns - 1] > t1 ? t1 : s.end[ns - 1];
-    const int nrows = int(w1 - t0 < tile ? w1 - t0 : tile);
-    if (nrows > 0) {
+    int nrows = int(w1 - t0 < tile ? w1 - t0 : tile);
+    if (nrows > tile / 4 || w1 == t1) {
       if (int(threadIdx.x) < nrows) {
         int lo = 0, hi = ns - 1;               // first segment of the window that ends behind e
         while (lo < hi) {
@@ -151,13 +156,22 @@ __device__ __forceinline__ void tb_tiles(TbTile& s, const int32_t* __restrict__ 
         s.dt[threadIdx.x] = s.tdst[lo] - te;
         if (int(threadIdx.x) == nrows - 1) s.next = lo;
       }
-      __syncthreads();
-      f(t0, nrows);
-      t0 += nrows;
-      seg += s.next;
-    } else {
-      seg += ns;                               // seg + ns < N: only empty segments in the window
+    } else {                                   // the same in memory, over all segments from seg on
+      nrows = int(t1 - t0 < tile ? t1 - t0 : tile);
+      if (int(threadIdx.x) < nrows) {
+        int64_t lo = seg, hi = N - 1;
+        while (lo < hi) {
+          const int64_t mid = (lo + hi) >> 1;
+          if (int64_t(off[mid + 1]) > e) hi = mid; else lo = mid + 1;
+        }
+        s.dt[threadIdx.x] = dst_t[lo] - te;
+        if (int(threadIdx.x) == nrows - 1) s.next = lo - seg;
+      }
     }
+    __syncthreads();
+    f(t0, nrows);
+    t0 += nrows;
+    seg += s.next;
     __syncthreads();
   }
 }

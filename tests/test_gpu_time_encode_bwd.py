@@ -121,6 +121,55 @@ def test_time_encode_bwd_edge_ranges(counts):
     assert_close(got[1], ref[1], "f32", "dphi")
 
 
+def _sparse_block(N, E, seed):
+    """N destinations that share E edges among them: offsets, query times, edge times."""
+    r = np.random.default_rng(seed)
+    counts = np.bincount(r.integers(0, N, E), minlength=N)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    return off, (r.random(N) * 1e4).astype(np.float32), (r.random(E) * 1e3).astype(np.float32)
+
+
+@pytest.mark.parametrize("N,E", [(1_000_000, 1000), (1_000_000, 1), (300_000, 9000), (40_000, 39_000),
+                                 (20_000, 60_000)])
+def test_time_encode_bwd_mostly_empty_segments(N, E):
+    """Rows within a tile's window of segments and far behind it, in one tile and in several."""
+    _announce(f"time encode bwd sparse N={N} E={E}")
+    off, dst_t, edge_t = _sparse_block(N, E, N + E)
+    om, ph = omega_phi(20)
+    dte = _randn((E, 20), "f32", "cuda", 6)
+    got = _tb_gpu(off, dst_t, edge_t, om, ph, dte)
+    ref = oracle.time_encode_bwd(off, dst_t, edge_t, om, ph, dte.double().cpu().numpy())
+    assert_close(got[0], ref[0], "f32", "domega")
+    assert_close(got[1], ref[1], "f32", "dphi")
+
+
+def test_time_encode_bwd_empty_segments_cost_little():
+    """1000 edges among 4e6 destinations take about as long as among 100: the workgroups do not walk the
+    empty segments (walked 256 at a time by 8 workgroups they took 100 times as long)."""
+    _announce("time encode bwd time of empty segments")
+    om, ph = map(to_dev, omega_phi(100))
+    dte = _randn((1000, 100), "f32", "cuda", 7)
+    dw, dp = torch.zeros(100, device="cuda"), torch.zeros(100, device="cuda")
+    took = {}
+    for N in (100, 4_000_000):
+        off, dst_t, edge_t = (to_dev(x) for x in _sparse_block(N, 1000, N))
+        g = fast.tcsr(off, 1000, edge_t=edge_t, dst_t=dst_t)
+        wsb = fast.fast_time_encode_bwd_workspace(N, 100)
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                fast.fast_time_encode_bwd(g, om, ph, 100, dte, fast.F32, dw, dp, ws, wsb)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 5)
+        took[N] = min(times)
+    print(f"[time] {took}", flush=True)
+    assert took[4_000_000] < 15 * took[100], took
+
+
 def test_time_encode_bwd_no_edges_writes_zeros():
     _announce("time encode bwd without edges")
     off = np.zeros(6, np.int32)
