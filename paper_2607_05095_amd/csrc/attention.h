@@ -376,18 +376,29 @@ __device__ __forceinline__ void bwd_chunk(const AttnArgs& a, const LaneMap<P>& m
   const T* K = static_cast<const T*>(a.K);
   const T* V = static_cast<const T*>(a.V);
   Raw<T, VE> kr[ATT_CH_BWD][P], vr[ATT_CH_BWD][P];
+  // Indexed rows of a full chunk are loaded without a branch per slot: 66,000
+  // segments of 20 edges, bf16 4 x 32, 242.5 -> 239 us.  (The forward gains from
+  // the branches there too: 119 us without, 99 with them.)
+  if (IDX && __all(base + ATT_CH_BWD <= e1)) {
 #pragma unroll
-  for (int i = 0; i < ATT_CH_BWD; ++i) {
-    if (!__any(base + i < e1)) {
+    for (int i = 0; i < ATT_CH_BWD; ++i) {
+      load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, base + i), ld, m, kr[i]);
+      load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, base + i), ld, m, vr[i]);
+    }
+  } else {
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        kr[i][p].zero();
-        vr[i][p].zero();
+    for (int i = 0; i < ATT_CH_BWD; ++i) {
+      if (!__any(base + i < e1)) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          kr[i][p].zero();
+          vr[i][p].zero();
+        }
+      } else {
+        const int64_t e = slot_row(base, i, e1);
+        load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
+        load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
       }
-    } else {
-      const int64_t e = slot_row(base, i, e1);
-      load_raw<T, VE, P, NT && !IDX>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kr[i]);
-      load_raw<T, VE, P, NT && !IDX>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vr[i]);
     }
   }
   float t[ATT_CH_BWD], cm = -INFINITY;

@@ -135,15 +135,25 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd_rm(Attn
     // them once, and alone it ran 0.422 -> 0.396 ms on packed rows of the
     // 1e7-node batch's layer-1 block.  (Indexed rows are shared by several
     // segments and stay cacheable.)
+    // Indexed rows of a full chunk are loaded without a branch per slot: the
+    // branches cost the index loads 1 % (2.64 M edges 413 -> 405 us).
+    if (IDX && __all(base + RM_CH_FWD <= e1)) {
 #pragma unroll
-    for (int i = 0; i < RM_CH_FWD; ++i) {
-      if (!__any(base + i < e1)) {
+      for (int i = 0; i < RM_CH_FWD; ++i) {
+        rm_load_row<!IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, base + i), ld, m, kx[i]);
+        rm_load_row<!IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, base + i), ld, m, vx[i]);
+      }
+    } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
-      } else {
-        const int64_t e = slot_row(base, i, e1);
-        rm_load_row<!IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
-        rm_load_row<!IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+      for (int i = 0; i < RM_CH_FWD; ++i) {
+        if (!__any(base + i < e1)) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
+        } else {
+          const int64_t e = slot_row(base, i, e1);
+          rm_load_row<!IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
+          rm_load_row<!IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+        }
       }
     }
     float t[RM_CH_FWD][H], cm[H];
@@ -204,7 +214,12 @@ struct RmBwdState {
   float mx[H], Z[H], Dn[H];  // reference point (log2 units), sum w, sum w dalpha
 };
 
-template <int H, int G, bool NT, bool IDX>
+// FULL: every segment of the wave has all of the chunk's edges.  With indexed
+// rows such a chunk is a path of its own, without a branch per slot between
+// the index and row loads and without masks (2.64 M edges, 2 x 50, branches and
+// masks / re-reads and masks / so: per-edge gradients 1344 / 1314 / 1295 us,
+// coefficients 1035 / 992 / 978).
+template <int H, int G, bool NT, bool IDX, bool FULL>
 __device__ __forceinline__ void rm_bwd_chunk(const AttnArgs& a, const RmMap<H>& m, int64_t base,
                                              int64_t e1, bool has_lse, float sl2,
                                              RmBwdState<H>& S, float (&x)[RM_CH_BWD][H],
@@ -213,15 +228,23 @@ __device__ __forceinline__ void rm_bwd_chunk(const AttnArgs& a, const RmMap<H>& 
   const float* K = static_cast<const float*>(a.K);
   const float* V = static_cast<const float*>(a.V);
   float kx[RM_CH_BWD][4], vx[RM_CH_BWD][4];
+  if (FULL) {
 #pragma unroll
-  for (int i = 0; i < RM_CH_BWD; ++i) {
-    if (!__any(base + i < e1)) {
+    for (int i = 0; i < RM_CH_BWD; ++i) {
+      rm_load_row<NT && !IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, base + i), ld, m, kx[i]);
+      rm_load_row<NT && !IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, base + i), ld, m, vx[i]);
+    }
+  } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
-    } else {
-      const int64_t e = slot_row(base, i, e1);
-      rm_load_row<NT && !IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
-      rm_load_row<NT && !IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+    for (int i = 0; i < RM_CH_BWD; ++i) {
+      if (!__any(base + i < e1)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) kx[i][k] = vx[i][k] = 0.f;
+      } else {
+        const int64_t e = slot_row(base, i, e1);
+        rm_load_row<NT && !IDX, H>(K, operand_row<IDX>(a.kidx, a.k_rows, e), ld, m, kx[i]);
+        rm_load_row<NT && !IDX, H>(V, operand_row<IDX>(a.vidx, a.v_rows, e), ld, m, vx[i]);
+      }
     }
   }
   float t[RM_CH_BWD][H], cm[H];
@@ -235,10 +258,15 @@ __device__ __forceinline__ void rm_bwd_chunk(const AttnArgs& a, const RmMap<H>& 
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       x[i][h] = d[h] * sl2;
-      da[i][h] = base + i < e1 ? da[i][h] : 0.f;
-      t[i][h] = base + i < e1 ? lrelu(x[i][h], a.slope) : -INFINITY;
+      t[i][h] = FULL || base + i < e1 ? lrelu(x[i][h], a.slope) : -INFINITY;
       cm[h] = fmaxf(cm[h], t[i][h]);
     }
+  }
+  if (!FULL && __any(base + RM_CH_BWD > e1)) {           // masked slots add nothing
+#pragma unroll
+    for (int i = 0; i < RM_CH_BWD; ++i)
+#pragma unroll
+      for (int h = 0; h < H; ++h) da[i][h] = base + i < e1 ? da[i][h] : 0.f;
   }
   if (!has_lse) {
     float corr[H];
@@ -342,11 +370,18 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_bwd_rm(Attn
 #pragma unroll
   for (int c = 0; c < ATT_RM_NSAVE; ++c) {
     const int64_t base = e0 + c * RM_CH_BWD;
-    if (base < e1) rm_bwd_chunk<H, G, NT, IDX>(a, m, base, e1, has_lse, sl2, S, st[c], sda[c]);
+    if (base >= e1) continue;
+    if constexpr (IDX) {
+      if (__all(base + RM_CH_BWD <= e1)) {
+        rm_bwd_chunk<H, G, NT, IDX, true>(a, m, base, e1, has_lse, sl2, S, st[c], sda[c]);
+        continue;
+      }
+    }
+    rm_bwd_chunk<H, G, NT, IDX, false>(a, m, base, e1, has_lse, sl2, S, st[c], sda[c]);
   }
   for (int64_t base = e0 + ATT_RM_NSAVE * RM_CH_BWD; base < e1; base += RM_CH_BWD) {
     float tt[RM_CH_BWD][H], td[RM_CH_BWD][H];
-    rm_bwd_chunk<H, G, NT, IDX>(a, m, base, e1, has_lse, sl2, S, tt, td);
+    rm_bwd_chunk<H, G, NT, IDX, false>(a, m, base, e1, has_lse, sl2, S, tt, td);
   }
 
   // dQ = scale/Z * (A - D B), per element with its head's Z and D

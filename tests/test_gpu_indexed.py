@@ -294,6 +294,46 @@ def test_identity_index_equals_plain_operator():
         assert torch.equal(a, c)
 
 
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (2, 14, "f32"), (2, 102, "f32"), (4, 32, "bf16"),
+                                     (1, 16, "f32"), (3, 13, "f32")])
+def test_indexed_full_and_partial_chunks(H, dh, dt):
+    """Waves whose segments all have a whole chunk of edges, waves where one of them lacks an edge, and
+    both in turn along long segments: as the plain operators on the gathered rows."""
+    _announce(f"indexed full and partial chunks {H}x{dh} {dt}")
+    counts = np.array([10] * 9 + [5] * 8 + [10, 9] * 5 + [20] * 8 + [5, 6, 4, 0] * 4 + [25, 30, 31, 15, 1, 10] * 3)
+    N, E, U = counts.size, int(counts.sum()), 97
+    r = np.random.default_rng(H * dh)
+    g = fast.tcsr(to_dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)), E)
+    ki, vi = (to_dev(r.integers(0, U, E).astype(np.int32)) for _ in range(2))
+    Q, K, V, dO = (_randn((n, H, dh), dt, "cuda", 60 + j) for j, n in enumerate((N, U, U, N)))
+    Kg, Vg = K[ki.long()].contiguous(), V[vi.long()].contiguous()
+    scale, code = float(np.float32(1 / np.sqrt(dh))), DT[dt]
+    res = []
+    for indexed in (False, True):
+        out, dQ, dK, dV = (torch.empty((n, H, dh), device="cuda", dtype=tdtype(dt)) for n in (N, N, E, E))
+        lse, ge, ae = (torch.empty((n, H), device="cuda") for n in (N, E, E))
+        if indexed:
+            ops = (Q, K, ki, U, V, vi, U, scale, SLOPE)
+            fast.fast_edge_attention_fwd_indexed(g, H, dh, code, *ops, out, lse)
+            fast.fast_edge_attention_bwd_indexed(g, H, dh, code, *ops, lse, dO, dQ, dK, dV)
+            dQc = torch.empty_like(dQ)
+            fast.fast_edge_attention_bwd_indexed_coef(g, H, dh, code, *ops, lse, dO, dQc, ge, ae)
+            assert torch.equal(dQ, dQc)
+        else:
+            fast.fast_edge_attention_fwd(g, H, dh, code, Q, Kg, Vg, scale, SLOPE, out, lse)
+            fast.fast_edge_attention_bwd(g, H, dh, code, Q, Kg, Vg, scale, SLOPE, lse, dO, dQ, dK, dV)
+        torch.cuda.synchronize()
+        res.append((out, lse, dQ, dK, dV))
+    for name, a, c in zip(("out", "lse", "dQ", "dK", "dV"), *res):
+        if name == "lse":                                   # -inf without edges
+            assert torch.equal(torch.isinf(a), torch.isinf(c))
+            a, c = (torch.where(torch.isinf(x), 0.0, x) for x in (a, c))
+        assert_close(c, _host(a), "f32" if name == "lse" else dt, f"{name} {H}x{dh}")
+    seg = torch.repeat_interleave(torch.arange(N, device="cuda"), to_dev(counts))
+    assert_close((ge[..., None] * Q[seg].float()), _host(res[1][3]), dt, "dK from coefficients")
+    assert_close((ae[..., None] * dO[seg].float()), _host(res[1][4]), dt, "dV from coefficients")
+
+
 def test_index_add_rows_malformed_lists_stay_in_bounds():
     """Occurrence offsets that decrease or leave [0, n] and positions outside
     [0, n) give unspecified sums, but every access stays in range: the call
