@@ -527,6 +527,7 @@ struct PlainRows {
   __device__ void chunk(int) {}
   __device__ Pos pos(int32_t p) const { return Pos{int32_t(clamp64(p, 0, n - 1))}; }
   __device__ static Pos from_lane(const Pos& k, int r, int lanes) { return Pos{__shfl(k.p, r, lanes)}; }
+  template <bool SPACED>
   __device__ Item fetch(const Pos& k, int c) const {
     // each source row is read once per call: streaming (non-temporal)
     // loads, as for the output rows below (1e7-node batch, K / V indices 0.41 /
@@ -571,12 +572,17 @@ struct ScaledRows {
   __device__ static Pos from_lane(const Pos& k, int r, int lanes) {
     return Pos{__shfl(k.p, r, lanes), __shfl(k.v, r, lanes)};
   }
+  template <bool SPACED>
   __device__ Item fetch(const Pos& k, int c) const {
     Item it;
     it.r.template load<false>(src + int64_t(k.v) * D + c * VE);
     const int32_t* __restrict__ s = rec + int64_t(k.p) * (1 + H) + 1;
     it.s0 = __int_as_float(s[h0]);
-    it.s1 = dh % VE ? __int_as_float(s[h1]) : it.s0;
+    // The branch waits for s0 before the next row is asked for.  A stream of
+    // short rows is faster so (1.32 M edges into 1.25 M rows, bf16 4 x 32: 227 us,
+    // 257 without), long rows slower (6000 positions in 100 rows 49 us, 36
+    // without): they load s1 also where it is s0.
+    it.s1 = !SPACED || dh % VE ? __int_as_float(s[h1]) : it.s0;
     return it;
   }
   __device__ void add(double (&acc)[VE], const Item& it) const {
@@ -592,18 +598,29 @@ struct ScaledRows {
 // calls it.  The group's lanes look up a position each -- one load, whatever
 // its count -- and then pass them round, so that the rows of U positions are
 // in flight together, also where a row has fewer than U of them.  In groups
-// of fewer than 8 lanes (rows of a few elements) every lane looks up all.
-template <int VE, class Src, int U>
+// of fewer than 16 lanes every lane looks up all: as many positions as lanes
+// are too few in flight for a hub's pieces, and a mask per position in the
+// loop breaks up the loads (2.64 M positions x 1 in 65,536 rows 202 -> 133 us,
+// 600 x 20 bf16 in 100 rows 30 -> 25).  WIDE: groups of 16 lanes and more only.
+template <int VE, class Src, int U, bool WIDE = false>
 __device__ __forceinline__ void ia_sum(const int32_t* __restrict__ occ, int64_t j0, int64_t j1, int c,
                                        bool on, int l, int lanes, const Src& src, double (&acc)[VE]) {
-  if (lanes < 8) {
-    for (int64_t j = j0; j < j1; j += U) {
-      typename Src::Item x[U];
+  if (!WIDE && lanes < 16) {
+    constexpr int S = U < 16 ? 4 : U;           // more in flight cost the short rows their occupancy
+    typename Src::Item x[S];
+    int64_t j = j0;
+    for (; j + S <= j1; j += S) {
 #pragma unroll
-      for (int r = 0; r < U; ++r)
-        if (on && j + r < j1) x[r] = src.fetch(src.pos(occ[j + r]), c);
+      for (int r = 0; r < S; ++r) x[r] = src.template fetch<false>(src.pos(occ[j + r]), c);
 #pragma unroll
-      for (int r = 0; r < U; ++r)
+      for (int r = 0; r < S; ++r) src.add(acc, x[r]);
+    }
+    for (; j < j1; j += 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (j + r < j1) x[r] = src.template fetch<false>(src.pos(occ[j + r]), c);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
         if (j + r < j1) src.add(acc, x[r]);
     }
     return;
@@ -613,14 +630,21 @@ __device__ __forceinline__ void ia_sum(const int32_t* __restrict__ occ, int64_t 
     const typename Src::Pos mine = src.pos(occ[jb + (l < m ? l : m - 1)]);
     for (int r0 = 0; r0 < m; r0 += U) {
       typename Src::Item x[U];
+      if (r0 + U <= m) {
 #pragma unroll
-      for (int r = 0; r < U; ++r) {
-        const typename Src::Pos k = Src::from_lane(mine, (r0 + r) & (lanes - 1), lanes);
-        if (on && r0 + r < m) x[r] = src.fetch(k, c);
+        for (int r = 0; r < U; ++r) x[r] = src.template fetch<false>(Src::from_lane(mine, r0 + r, lanes), c);
+#pragma unroll
+        for (int r = 0; r < U; ++r) src.add(acc, x[r]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+          const typename Src::Pos k = Src::from_lane(mine, (r0 + r) & (lanes - 1), lanes);
+          if (on && r0 + r < m) x[r] = src.template fetch<false>(k, c);
+        }
+#pragma unroll
+        for (int r = 0; r < U; ++r)
+          if (r0 + r < m) src.add(acc, x[r]);
       }
-#pragma unroll
-      for (int r = 0; r < U; ++r)
-        if (r0 + r < m) src.add(acc, x[r]);
     }
   }
 }
@@ -657,7 +681,7 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_pieces(
     double acc[VE];
 #pragma unroll
     for (int t = 0; t < VE; ++t) acc[t] = 0.0;
-    ia_sum<VE, Src, Src::PIECE_UNROLL>(occ, j0, j1, c, on, l, lanes, src, acc);
+    ia_sum<VE, Src, Src::PIECE_UNROLL>(occ, j0, j1, on ? c : 0, on, l, lanes, src, acc);
 #pragma unroll
     for (int t = 0; t < VE; ++t)
       if (on) partial[q * D + c * VE + t] = acc[t];
@@ -789,7 +813,7 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_rows(
         double acc[VE];
 #pragma unroll
         for (int t = 0; t < VE; ++t) acc[t] = 0.0;
-        ia_sum<VE, Src, Src::ROW_UNROLL>(occ, j0, j1, c, on, l, lanes, src, acc);
+        ia_sum<VE, Src, Src::ROW_UNROLL, (R > 1)>(occ, j0, j1, on ? c : 0, on, l, lanes, src, acc);
         if (on) ia_store<VE>(dst + u * D + c * VE, acc);
       }
     }
@@ -798,6 +822,13 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_rows(
   const int64_t j0 = __shfl(lo, 0, lanes);
   const int ends = int(hi - j0);                            // lane r: end of row r, from the first position
   const int total = __shfl(ends, nr - 1, lanes);            // at most R * IA_PIECE
+  if constexpr (VE >= 4) {
+    if (total == 0) {   // rows without occurrences: one run of zeros (3e6 such rows x 128: 715 -> 300 us)
+      const float zero[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int k = l; k < nr * D / 4; k += lanes) StreamIO<float, 4, true>::store(dst + u0 * D + 4 * k, zero);
+      return;
+    }
+  }
   for (int c0 = 0; c0 < chunks; c0 += lanes) {
     const int c = c0 + l;
     const bool on = c < chunks;
@@ -815,7 +846,7 @@ __global__ void __launch_bounds__(IA_THREADS) k_ia_rows(
 #pragma unroll
         for (int r = 0; r < Src::ROW_UNROLL; ++r) {
           const typename Src::Pos k = Src::from_lane(mine, (r0 + r) & (lanes - 1), lanes);
-          if (on && r0 + r < m) x[r] = src.fetch(k, c);
+          if (on && r0 + r < m) x[r] = src.template fetch<true>(k, c);
         }
 #pragma unroll
         for (int r = 0; r < Src::ROW_UNROLL; ++r) {
@@ -954,8 +985,11 @@ static hipError_t ia_launch(const int32_t* occ_off, const int32_t* occ, int64_t 
   const int64_t np_blocks = (mb + groups_per_block - 1) / groups_per_block;
   const int64_t ng_blocks = (gb + groups_per_block - 1) / groups_per_block;
   // IA_ROWS rows per group where that leaves the chip enough groups (below,
-  // a group per row fills it better) and a group has a lane for each bound
-  const bool many = lanes >= 4 * IA_ROWS && num_rows >= IA_ROWS * IA_GROUPS_FILL;
+  // a group per row fills it better) and a group has a lane for each bound;
+  // rows of 8 positions and more fill a group's loads by themselves (2.64 M
+  // fp32 2 x 50 positions over 65,536 / 200,000 / 400,000 / 1e6 uniform rows, a
+  // row / 4 rows per group: 260 / 282, 268 / 294, 314 / 309, 460 / 343 us)
+  const bool many = lanes >= 4 * IA_ROWS && num_rows >= IA_ROWS * IA_GROUPS_FILL && n < 8 * num_rows;
   const int R = many ? IA_ROWS : 1;
   const int64_t nr_blocks = ((num_rows + R - 1) / R + groups_per_block - 1) / groups_per_block;
   if (n > IA_PIECE) {

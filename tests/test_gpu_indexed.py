@@ -462,3 +462,27 @@ def test_row_sums_of_large_outputs(H, dh, dt, rows):
     bad = off.clone()                       # malformed lists of this size stay in bounds too
     bad[::7] = torch.as_tensor(r.integers(-5, n + 6, bad[::7].numel()).astype(np.int32), device="cuda")
     assert torch.equal(_index_add_gpu(bad, occ, n, rows, src), _index_add_gpu(bad, occ, n, rows, src))
+
+
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (4, 32, "bf16"), (1, 20, "bf16"), (1, 7, "f32"), (1, 1, "f32"),
+                                     (1, 56, "f32"), (1, 64, "f32")])
+@pytest.mark.parametrize("rows,mean", [(70_001, 0.01), (65_536, 7.9), (65_536, 8.0), (700, 30.0)])
+def test_row_sums_empty_and_dense_outputs(H, dh, dt, rows, mean):
+    """Outputs of almost no positions (groups of rows without any, the last of them incomplete), of just
+    under and of 8 per row (where rows stop sharing a group of lanes), and of full ones, over
+    lane groups of 1 to 32."""
+    _announce(f"row sums rows={rows} mean={mean} {H}x{dh} {dt}")
+    r = np.random.default_rng(rows + H * dh)
+    n = int(rows * mean)
+    idx = r.integers(0, rows, n).astype(np.int32)
+    idx[:n // 50] = rows - 1 if mean < 1 else rows // 2          # a hub
+    off, occ = _occ_gpu(idx, rows)
+    src = _randn((n, H * dh), dt, "cuda", rows + H)
+    assert_close(_index_add_gpu(off, occ, n, rows, src), oracle.index_add_rows(idx, rows, _host(src)), "f32",
+                 "plain sums")
+    dst_off = np.minimum(np.arange(n // 3 + 2) * 3, n).astype(np.int32)
+    N = dst_off.size - 1
+    scal, q = _randn((n, H), "f32", "cuda", 5), _randn((N, H, dh), dt, "cuda", 6)
+    got = _scaled_rows_gpu(off, occ, n, rows, to_dev(dst_off), N, H, dh, scal, q)
+    assert_close(got, oracle.index_add_scaled_rows(idx, dst_off, rows, scal.cpu().numpy(), _host(q)), "f32",
+                 "scaled sums")
