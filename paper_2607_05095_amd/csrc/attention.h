@@ -684,6 +684,9 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_fwd(AttnArgs a) {
 // The first chunk is loaded before D is known.
 template <typename T, int VE, int P, int LPH_CT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
+  // Lanes per head known at run time only: ten rows and ten scalars in flight
+  // take 180 registers (100,000 segments of one edge, fp32 8 x 16: 85 us; 39 so).
+  constexpr int CH = LPH_CT > 0 ? ATT_CH_FWD : ATT_CH_BWD;
   LaneMap<P> m;
   if (!lane_setup<VE, P, LPH_CT>(a, m)) return;
   const int F = a.L.F, H = a.L.H;
@@ -692,16 +695,16 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
   load_row<T, VE, P>(static_cast<const T*>(a.Q), m.seg, F, m, q);
   int64_t e0, e1;
   seg_range(a, m.seg, e0, e1);
-  LaneScalars<LPH_CT, ATT_CH_FWD> al, da;
-  Raw<T, VE> kr[ATT_CH_FWD][P];
+  LaneScalars<LPH_CT, CH> al, da;
+  Raw<T, VE> kr[CH][P];
   al.load(a.alpha_in, e0, e1, H, m);
   da.load(a.dalpha_in, e0, e1, H, m);
-  load_rows<T, VE, P, ATT_CH_FWD>(K, e0, e1, F, m, kr);
+  load_rows<T, VE, P, CH>(K, e0, e1, F, m, kr);
   float D = 0.f;
 #pragma unroll
   for (int s = 0; s < al.N; ++s) D = fmaf(al.v[s], da.v[s], D);
-  for (int64_t base = e0 + ATT_CH_FWD; base < e1; base += ATT_CH_FWD) {
-    LaneScalars<LPH_CT, ATT_CH_FWD> x, y;
+  for (int64_t base = e0 + CH; base < e1; base += CH) {
+    LaneScalars<LPH_CT, CH> x, y;
     x.load(a.alpha_in, base, e1, H, m);
     y.load(a.dalpha_in, base, e1, H, m);
 #pragma unroll
@@ -710,16 +713,16 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
   if constexpr (LPH_CT > 0) D = group_sum_ct<LPH_CT>(D);   // else every lane summed all entries
   float dq[P][VE];
   FAST_ZERO(dq);
-  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
+  for (int64_t base = e0; base < e1; base += CH) {
     if (base != e0) {
       al.load(a.alpha_in, base, e1, H, m);
       da.load(a.dalpha_in, base, e1, H, m);
-      load_rows<T, VE, P, ATT_CH_FWD>(K, base, e1, F, m, kr);
+      load_rows<T, VE, P, CH>(K, base, e1, F, m, kr);
     }
 #pragma unroll
     for (int s = 0; s < al.N; ++s) al.v[s] *= da.v[s] - D;   // 0 past the segment's end
 #pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) {
+    for (int i = 0; i < CH; ++i) {
       if (base + i >= e1) break;
       float kx[P][VE], dk[P][VE];
       unpack_row<T, VE, P>(kr[i], kx);
@@ -773,6 +776,7 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_fwd(AttnArgs a) {
 // ============================================================ aggregation bwd
 template <typename T, int VE, int P, int LPH_CT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_bwd(AttnArgs a) {
+  constexpr int CH = LPH_CT > 0 ? ATT_CH_FWD : ATT_CH_BWD;
   LaneMap<P> m;
   if (!lane_setup<VE, P, LPH_CT>(a, m)) return;
   const int F = a.L.F, H = a.L.H;
@@ -781,14 +785,14 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_bwd(AttnArgs a) {
   load_row<T, VE, P>(static_cast<const T*>(a.dO), m.seg, F, m, go);
   int64_t e0, e1;
   seg_range(a, m.seg, e0, e1);
-  for (int64_t base = e0; base < e1; base += ATT_CH_FWD) {
-    LaneScalars<LPH_CT, ATT_CH_FWD> al, da;
-    Raw<T, VE> vr[ATT_CH_FWD][P];
+  for (int64_t base = e0; base < e1; base += CH) {
+    LaneScalars<LPH_CT, CH> al, da;
+    Raw<T, VE> vr[CH][P];
     al.load(a.alpha_in, base, e1, H, m);
-    load_rows<T, VE, P, ATT_CH_FWD>(V, base, e1, F, m, vr);
+    load_rows<T, VE, P, CH>(V, base, e1, F, m, vr);
     da.zero();
 #pragma unroll
-    for (int i = 0; i < ATT_CH_FWD; ++i) {
+    for (int i = 0; i < CH; ++i) {
       float vx[P][VE], dv[P][VE];
       unpack_row<T, VE, P>(vr[i], vx);
       da.put(i, head_dot<VE, P, LPH_CT>(go, vx, m.lph), m);

@@ -135,10 +135,15 @@ fast_status_t attn_run(const char* fn, Op op, const fast_tcsr_t* g, int H, int d
                 (long long)a.ldkv, a.L.F);
   // fp32 rows whose heads break the 16-byte alignment (dh % 4 != 0) but whose
   // width does not (F % 4 == 0): row-major lanes, so every row moves as
-  // 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).
+  // 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).  The separate
+  // operators only where a row fills more than half of the least 16 lanes: the
+  // four of them on 66,000 ragged segments of 2 x 6 / 2 x 10 / 2 x 14 / 2 x 18, us,
+  // head-major 44 / 69 / 71 / 110, row-major 74 / 78 / 82 / 85.
+  const bool fused_op = op == Op::kAttnFwd || op == Op::kAttnBwd || op == Op::kAttnFwdIdx ||
+                        op == Op::kAttnBwdIdx;
   a.L.rm = false;
   if (rowmajor_enabled() && dt == FAST_F32 && H == 2 && dh % 4 != 0 &&
-      (H * dh) % 4 == 0 && (H * dh) / 4 <= 64) {
+      (H * dh) % 4 == 0 && (H * dh) / 4 <= 64 && (fused_op || (H * dh) / 4 > 8)) {
     bool al = true;
     for (int k = 0; k < nrows; ++k)
       if (rows[k] && !aligned(rows[k], 16)) al = false;

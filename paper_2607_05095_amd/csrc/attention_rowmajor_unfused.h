@@ -69,6 +69,13 @@ __device__ __forceinline__ void ru_logits(const float (&q)[4], const float (&kx)
                                           float slope, float (&t)[RU_CH][H]) {
 #pragma unroll
   for (int i = 0; i < RU_CH; ++i) {
+    if (i == RU_CH / 2 && !__any(base + i < e1)) {
+#pragma unroll
+      for (int k = RU_CH / 2; k < RU_CH; ++k)
+#pragma unroll
+        for (int h = 0; h < H; ++h) t[k][h] = -INFINITY;
+      break;
+    }
     float d[H];
     rm_dots<H, G>(q, kx[i], m, d);
 #pragma unroll
@@ -269,6 +276,7 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_bwd_rm(AttnArgs a) {
     for (int j = 0; j < da.N; ++j) da.v[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < RU_CH; ++i) {
+      if (i == RU_CH / 2 && !__any(base + i < e1)) break;
       float d[H], w[H], dv[4];
       rm_dots<H, G>(go, vx[i], m, d);
 #pragma unroll

@@ -220,7 +220,8 @@ def test_attention_edge_cases(name, counts, H, dh, dt):
 
 
 @pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (2, 30, "f32"), (2, 102, "f32"), (4, 32, "f32"),
-                                     (4, 32, "bf16"), (3, 13, "f32"), (1, 128, "bf16")])
+                                     (4, 32, "bf16"), (3, 13, "f32"), (1, 128, "bf16"), (8, 16, "f32"),
+                                     (2, 14, "f32"), (2, 18, "f32")])
 def test_attention_chunk_edges(H, dh, dt):
     """Degrees around the chunks of 4, 5 and 10 edges and the 20 logits the separate softmax keeps, next to
     segments of other degrees and empty ones (leading ones too) in the same wave; row-major groups
