@@ -513,6 +513,14 @@ constexpr int DS_THREADS = 1024;
 constexpr int DS_WAVES = DS_THREADS / 64;
 constexpr int DS_GROUP = 8;                      // words per rank base: two 16-byte LDS reads
 constexpr int DS_UNROLL = 8;                     // ids in flight per thread
+// Of them side by side in a batch of more than DS_RUN_IDS ids.  Of ascending ids
+// 32 lie in a bitmap word, and lanes that mark one word wait for each other: one
+// by one, us, ascending / random order / general paths, 16,000 ids of 1e6
+// 21 / 10.5 / 29 and 22, 32,768 35 / 12.5 / 20; four side by side 9.4 / 10.8 and
+// 11.5 / 13.  Smaller batches stay one by one: run by run takes more code, whose
+// fetch costs a small step 0.7 us a call (n = 14,590 and 16,390, Zipf: 8.8 -> 9.5).
+constexpr int DS_RUN = 4;
+constexpr int64_t DS_RUN_IDS = 20480;
 constexpr int DS_SLICE = 2048;                   // ids written per workgroup
 constexpr int64_t DS_MAX_WORDS = 32768;          // 128 KB of LDS: universes of 2^20 ids
 constexpr int64_t DS_MAX_IDS = 32768;
@@ -525,6 +533,7 @@ static bool small_batch(int64_t n, int64_t W) {
   return n > 0 && n <= DS_MAX_IDS && W > 0 && W <= DS_MAX_WORDS && mark_override() == 0;
 }
 
+template <int RUN>
 __global__ void __launch_bounds__(DS_THREADS) k_dedup_small(
     const int64_t* __restrict__ ids, int n, int64_t id_bound, int W, int64_t* __restrict__ uni,
     int32_t* __restrict__ inv, int64_t* __restrict__ num_unique, const int32_t* __restrict__ slot_map,
@@ -536,16 +545,44 @@ __global__ void __launch_bounds__(DS_THREADS) k_dedup_small(
   const int groups = (W + DS_GROUP - 1) / DS_GROUP;
   for (int j = threadIdx.x; j < groups * (DS_GROUP / 4); j += DS_THREADS) s_bm4[j] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  for (int i0 = threadIdx.x; i0 < n; i0 += DS_UNROLL * DS_THREADS) {
-    int64_t x[DS_UNROLL];
+  if constexpr (RUN == 1) {
+    for (int i0 = threadIdx.x; i0 < n; i0 += DS_UNROLL * DS_THREADS) {
+      int64_t x[DS_UNROLL];
 #pragma unroll
-    for (int r = 0; r < DS_UNROLL; ++r) x[r] = i0 + r * DS_THREADS < n ? ids[i0 + r * DS_THREADS] : int64_t(-1);
+      for (int r = 0; r < DS_UNROLL; ++r) x[r] = i0 + r * DS_THREADS < n ? ids[i0 + r * DS_THREADS] : int64_t(-1);
 #pragma unroll
-    for (int r = 0; r < DS_UNROLL; ++r)
-      if (x[r] >= 0 && x[r] < id_bound) {
-        const uint32_t bit = 1u << (x[r] & 31);
-        if (!(bm[x[r] >> 5] & bit)) atomicOr(&bm[x[r] >> 5], bit);
+      for (int r = 0; r < DS_UNROLL; ++r)
+        if (x[r] >= 0 && x[r] < id_bound) {
+          const uint32_t bit = 1u << (x[r] & 31);
+          if (!(bm[x[r] >> 5] & bit)) atomicOr(&bm[x[r] >> 5], bit);
+        }
+    }
+  } else {   // RUN ids side by side: those of one word are marked together
+    for (int b0 = 0; b0 < n; b0 += DS_UNROLL * DS_THREADS) {
+      int64_t x[DS_UNROLL / RUN][RUN];
+#pragma unroll
+      for (int r = 0; r < DS_UNROLL / RUN; ++r) {
+        const int i = b0 + (r * DS_THREADS + int(threadIdx.x)) * RUN;
+#pragma unroll
+        for (int k = 0; k < RUN; ++k) x[r][k] = i + k < n ? ids[i + k] : int64_t(-1);
       }
+#pragma unroll
+      for (int r = 0; r < DS_UNROLL / RUN; ++r) {
+        uint32_t word = 0u, bits = 0u;
+#pragma unroll
+        for (int k = 0; k < RUN; ++k) {
+          if (x[r][k] < 0 || x[r][k] >= id_bound) continue;
+          const uint32_t w = uint32_t(x[r][k] >> 5);
+          if (w != word) {
+            if (bits && (bits & ~bm[word])) atomicOr(&bm[word], bits);
+            word = w;
+            bits = 0u;
+          }
+          bits |= 1u << (x[r][k] & 31);
+        }
+        if (bits && (bits & ~bm[word])) atomicOr(&bm[word], bits);
+      }
+    }
   }
   __syncthreads();
   // base ranks: thread t owns groups t DS_PER ...
@@ -864,8 +901,9 @@ static fast_status_t dedup_gather_run(const char* fn, const int64_t* ids, int64_
   hipError_t e = hipSuccess;
   // 1. mark ids, 2. word ranks (exclusive popcount prefix) and u
   if (path == MARK_LDS) {   // ... and 3. uni, inv and slots
-    hipLaunchKernelGGL(k_dedup_small, dim3(uint32_t((n + DS_SLICE - 1) / DS_SLICE)), dim3(DS_THREADS), 0, st, ids, int(n), id_bound, int(W), uni,
-                       inv, num_unique, slot_map, slots, zero_miss);
+    const auto small = n <= DS_RUN_IDS ? k_dedup_small<1> : k_dedup_small<DS_RUN>;
+    hipLaunchKernelGGL(small, dim3(uint32_t((n + DS_SLICE - 1) / DS_SLICE)), dim3(DS_THREADS), 0, st,
+                       ids, int(n), id_bound, int(W), uni, inv, num_unique, slot_map, slots, zero_miss);
   } else if (path == MARK_BUCKETS) {
     const int B = int(p.B), nblk = int(p.nblk);
     if (nblk > 0) {

@@ -774,14 +774,34 @@ def test_dedup_small_batches(bound, n):
         assert np.array_equal(_bits(rows)[hit], ref_rows[hit])
 
 
+@pytest.mark.parametrize("n,bound", [(1, 5), (4097, 5000), (20_480, 2**20), (20_481, 30_000), (32_768, 40_000),
+                                     (32_767, 2**20)])
+@pytest.mark.parametrize("step", [1, -1, 3])
+def test_dedup_small_batches_in_order(n, bound, step):
+    """Ascending and descending ids, many of one bitmap word side by side, with a repeat and an id outside
+    the universe among them."""
+    _announce(f"dedup small batch in order n={n} bound={bound} step={step}")
+    ids = (np.arange(n, dtype=np.int64) * step) % bound
+    if n > 100:
+        ids[7::31], ids[5::97] = ids[6], -1
+    valid = ids >= 0
+    uni, inv, u, _, _, _ = _dedup(ids, bound, None)
+    ref_uni, ref_inv = oracle.dedup(ids[valid])
+    assert u == ref_uni.size and np.array_equal(uni, ref_uni)
+    assert np.array_equal(inv[valid], ref_inv) and np.all(inv[~valid] == -1)
+
+
 @pytest.mark.parametrize("bound,n", [(2**29, 3000), (2**31, 3000), (2**31 + 1, 3000), (2**33 + 5, 50_000),
-                                     (3 * 10**7 + 13, 300_000), (40_000, 1200), (2**31, 9_000_000)])
+                                     (3 * 10**7 + 13, 300_000), (40_000, 1200), (2**31, 9_000_000),
+                                     (2**20 + 1, 1200), (2**20 + 33, 32_768), (2**20, 32_769)])
 def test_dedup_sparse_universes(bound, n):
     """Universes far larger than the batch, on both sides of the largest one
     that bucketed marking takes (2^31 ids: 4096 buckets of 2^19) and up to
     2^33 ids (hashed marking), with Zipf-like hot ids (a few ids repeated in
     every workgroup's share), ids at both ends of the universe, and many
-    workgroups; 9 M ids over 2^31 give more (bucket, workgroup) counts than
+    workgroups; 2^20 ids and a few more with small batches, the smallest
+    bucketed marking (40,000 ids take one launch with the bitmap in LDS, 2^20
+    ids and 32,769 a byte map); 9 M ids over 2^31 give more (bucket, workgroup) counts than
     the bucketed marking takes (2^24), so they are marked by hashed atomics."""
     _announce(f"dedup sparse universe bound={bound} n={n}")
     r = np.random.default_rng(bound % 1000 + n)
