@@ -87,7 +87,7 @@ def test_access_count_and_selection_vs_oracle(cfg, k):
 
 @pytest.mark.parametrize("bound", [1000, 40])
 def test_access_count_repeats_invalid_ids_and_accumulation(bound):
-    # bound 1000 over ~4 ids a batch takes the stamp path, bound 40 the byte map
+    # bound 1000 over ~4 ids a batch takes the mask path, bound 40 the byte map
     _announce(f"access count edge cases bound={bound}")
     top = bound - 1
     batches = [np.array([5, 5, 5, top, 0, -1, bound, 7 << 40], np.int64),
@@ -127,6 +127,32 @@ def test_access_count_sparse_forms(bound, batches, size):
         u = np.unique(x)
         want[u[(u >= 0) & (u < bound)]] += 1
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("bound,batches,size,big", [
+    (40_000, 90, 5, 100_000),                    # no room for the large batch's stage: stamps, many workgroups
+    (40_000, 12, 5, 25_000),                     # the same with masks, in two groups
+    (1_000_000, 40, 100, 1_000_000),             # room for one batch a pass, its size set by the large one
+    ((1 << 28) + 1, 12, 20_000, 20_001),         # beyond the buckets: masks in two groups
+    ((1 << 28) + 1, 40, 2000, 20_001),           # beyond the buckets: stamps
+])
+def test_access_count_one_large_batch(bound, batches, size, big):
+    """Small batches with a large one among them, on the paths that a sparse universe takes when its
+    batches cannot be staged: ids repeated across workgroups and batches, ids outside the universe."""
+    _announce(f"access count bound={bound} batches={batches} size={size} one of {big}")
+    r = np.random.default_rng(bound % 1000 + batches)
+    bs = []
+    for k in range(batches):
+        x = r.integers(-2, bound + 2, big if k == batches // 2 else size)
+        x[r.random(x.size) < 0.3] = bound - 1 - 7 * (k % 3)
+        x[r.random(x.size) < 0.3] = r.integers(0, min(bound, 1000))
+        bs.append(x.astype(np.int64))
+    got = _count_gpu(bs, bound)
+    want = np.zeros(bound, np.int32)
+    for x in bs:
+        u = np.unique(x)
+        want[u[(u >= 0) & (u < bound)]] += 1
+    assert np.array_equal(got.cpu().numpy(), want)
 
 
 def test_selection_edge_cases():

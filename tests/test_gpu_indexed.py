@@ -351,6 +351,38 @@ def test_index_add_rows_malformed_lists_stay_in_bounds():
 
 
 # ------------------------------------------------------------------ coefficient form
+@pytest.mark.parametrize("rows,D", [(500, 8), (70_000, 100)])
+def test_index_add_rows_malformed_lists_write_nothing_else(rows, D):
+    """Malformed occurrence offsets and positions: nothing outside dst and the workspace is written, and
+    short rows whose own offsets and positions are intact still get their sums."""
+    _announce(f"index add with malformed lists, guarded, rows={rows} D={D}")
+    r = np.random.default_rng(rows)
+    cnt = r.integers(0, 12, rows)
+    off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    n = int(off[-1])
+    occ = r.permutation(n).astype(np.int32)
+    bad = r.choice(rows + 1, rows // 20, replace=False)
+    off[bad] = r.integers(-n, 2 * n, bad.size).astype(np.int32)
+    occ_bad = r.random(n) < 0.01
+    occ[occ_bad] = r.choice([-1, -n, n, 2 * n], int(occ_bad.sum())).astype(np.int32)
+    src = _randn((n, D), "f32", "cuda", 13)
+    wsb = fast.fast_index_add_rows_workspace(n, rows, D)
+    guard = 4096
+    dst = torch.full((rows * D + 2 * guard,), 7.0, device="cuda")
+    ws = torch.full((wsb + 2 * guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    fast.fast_index_add_rows(to_dev(off), to_dev(occ), n, rows, D, fast.F32, src, dst[guard:], ws[guard:], wsb)
+    torch.cuda.synchronize()
+    for x, v, size in ((dst, 7.0, rows * D), (ws, 0xA5, wsb)):
+        assert (x[:guard] == v).all() and (x[guard + size:] == v).all()
+    got = dst[guard:guard + rows * D].view(rows, D).cpu().numpy()
+    ref = src.double().cpu().numpy()
+    whole = [u for u in range(rows) if 0 <= off[u] <= off[u + 1] <= n and off[u + 1] - off[u] <= 64
+             and not occ_bad[off[u]:off[u + 1]].any()]
+    assert len(whole) > rows // 2
+    want = np.stack([ref[occ[off[u]:off[u + 1]]].sum(0) for u in whole])
+    assert_close(got[whole], want, "f32", "rows with intact lists")
+
+
 def _scaled_rows_gpu(off_occ, occ, n, num_rows, dst_off, N, H, dh, scal, src):
     dst = torch.full((num_rows, H, dh), float("nan"), device="cuda")
     wsb = fast.fast_index_add_scaled_rows_workspace(n, num_rows, H, dh)

@@ -499,6 +499,23 @@ def test_csr_offsets_batched_bit_exact(case):
         assert np.array_equal(got, oracle.csr_offsets(c)), f"block {k}"
 
 
+def test_csr_offsets_batched_in_place():
+    """Offsets written over the counts they come from, in blocks of a few tiles: the later tiles must not
+    read counts that an earlier tile has replaced; a block whose offsets lie elsewhere beside them."""
+    _announce("offsets batched in place")
+    r = np.random.default_rng(8)
+    ns = [2048 * 6 + 5, 100, 2048 * 7, 5000]
+    lists = [r.integers(0, 30, n).astype(np.int32) for n in ns]
+    bufs = [to_dev(np.append(c, np.int32(-7))) for c in lists]
+    outs = bufs[:3] + [torch.full((5001,), -7, dtype=torch.int32, device="cuda")]
+    wsb = fast.fast_csr_offsets_batched_workspace(ns)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    fast.fast_csr_offsets_batched(bufs, ns, outs, ws, wsb)
+    torch.cuda.synchronize()
+    for k, (o, c) in enumerate(zip(outs, lists)):
+        assert np.array_equal(o.cpu().numpy(), oracle.csr_offsets(c)), f"block {k}"
+
+
 @pytest.mark.parametrize("seed", range(16))
 def test_csr_offsets_random(seed):
     """Seeded random layer-block sets: 1 to 12 blocks of 0 to 5e6 segments
