@@ -91,22 +91,33 @@ __device__ __forceinline__ void rm_store_row(float* __restrict__ base, int64_t r
 }
 
 // Per-head dot products of two rows: d[h] = sum over the row's elements of
-// head h, all-reduced over the G lanes of the group.
+// head h, all-reduced over the G lanes of the group.  Two heads of 4m + 2
+// elements: a lane's four belong to one head, or its first two to head 0 and
+// its last two to head 1.  Sums are selected, not products with 0: an
+// infinite element must not reach the other head.
 template <int H, int G>
 __device__ __forceinline__ void rm_dots(const float (&x)[4], const float (&y)[4], const RmMap<H>& m,
                                         float (&d)[H]) {
+  static_assert(H == 2, "elements 0, 1 and 2, 3 of a lane belong to one head each");
+  const float first = fmaf(x[1], y[1], x[0] * y[0]), last = fmaf(x[3], y[3], x[2] * y[2]);
+  const float all = fmaf(x[3], y[3], fmaf(x[2], y[2], first));
+  const float upper = m.hs[0] == m.hs[2] ? all : last;      // of the head of elements 2, 3
 #pragma unroll
-  for (int h = 0; h < H; ++h) {
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s = fmaf(m.hs[k] == h ? x[k] : 0.f, y[k], s);
-    d[h] = group_sum_ct<G>(s);
-  }
+  for (int h = 0; h < H; ++h)
+    d[h] = group_sum_ct<G>(m.hs[2] == h ? upper : (m.hs[0] == h ? first : 0.f));
 }
 
 // ============================================================ fused forward
+// Five waves per SIMD, though the registers would hold six: with six, full
+// chunks of packed rows stream slower (2.64 M edges 371 -> 383 us; ragged
+// segments gain, 100,000 of 2.4 edges 71 -> 62).
+#ifdef FAST_ATT_WAVES_PER_EU
+#define FAST_ATT_RM_FWD_OCC FAST_ATT_OCC
+#else
+#define FAST_ATT_RM_FWD_OCC __attribute__((amdgpu_waves_per_eu(5, 5)))
+#endif
 template <int H, int G, bool NT, bool IDX>
-__global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_OCC k_attn_fwd_rm(AttnArgs a) {
+__global__ void __launch_bounds__(ATT_MAX_BLOCK) FAST_ATT_RM_FWD_OCC k_attn_fwd_rm(AttnArgs a) {
   RmMap<H> m;
   if (!rm_setup<H, G>(a, m)) return;
   const int F = a.L.F, ld = int(a.ldkv);

@@ -281,6 +281,27 @@ def test_attention_infinite_values_stay_in_their_segment(H, dh, dt):
             np.testing.assert_allclose(r, x, rtol=tol, atol=tol, err_msg=f"{k} of segment {v} alone")
 
 
+@pytest.mark.parametrize("H,dh,dt", [(2, 50, "f32"), (2, 14, "f32"), (2, 30, "f32"), (2, 102, "f32"), (4, 32, "f32"),
+                                     (3, 13, "f32"), (2, 50, "bf16")])
+@pytest.mark.parametrize("short", [False, True])
+def test_attention_infinite_values_stay_in_their_head(H, dh, dt, short):
+    """Infinite entries of one head in every operand (among them the last before and the first after the
+    border of two heads) change nothing in the results of the others, at every entry point."""
+    _announce(f"attention infinite head {H}x{dh} {dt} short={short}")
+    counts = [3, 1, 0, 4, 2, 5] * 3 if short else [10, 7, 0, 13, 31, 5, 20, 9]
+    for head in (0, H - 1):
+        d = _synthetic_block(counts, H, dh, dt, seed=7)
+        want = _all_attention_results(d)
+        for name, at in (("Q", 1), ("K", 4), ("V", 5), ("V", 9), ("dO", 3)):
+            d.ops[name][at, head, dh - 1 if head == 0 else 0] = float("inf") if at % 2 else float("-inf")
+        got = _all_attention_results(d)
+        for h in range(H):
+            if h == head:
+                continue
+            for k in want:
+                np.testing.assert_array_equal(got[k][:, h], want[k][:, h], err_msg=f"{k} of head {h}")
+
+
 @pytest.mark.parametrize("slope", [-0.3, 0.0])
 @pytest.mark.parametrize("name,counts,H,dh,dt", [
     ("rowmajor_f32", [10, 1, 0, 7, 30, 10, 25, 3, 12], 2, 50, "f32"),
