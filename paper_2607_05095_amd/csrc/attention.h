@@ -681,12 +681,14 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_fwd(AttnArgs a) {
 }
 
 // ============================================================ edge softmax bwd
-// The first chunk is loaded before D is known.
-template <typename T, int VE, int P, int LPH_CT>
+// The first chunk is loaded before D is known.  SHORT: five edges a chunk, not
+// ten.  With lanes per head known at run time only, ten rows and all their
+// scalars in flight take 180 registers: the four operators on segments of one
+// edge / ragged ones / of ten edges, fp32 8 x 16, us, 214 / 191 / 439 with ten and
+// 135 / 142 / 454 with five.
+template <typename T, int VE, int P, int LPH_CT, bool SHORT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_softmax_bwd(AttnArgs a) {
-  // Lanes per head known at run time only: ten rows and ten scalars in flight
-  // take 180 registers (100,000 segments of one edge, fp32 8 x 16: 85 us; 39 so).
-  constexpr int CH = LPH_CT > 0 ? ATT_CH_FWD : ATT_CH_BWD;
+  constexpr int CH = SHORT ? ATT_CH_BWD : ATT_CH_FWD;
   LaneMap<P> m;
   if (!lane_setup<VE, P, LPH_CT>(a, m)) return;
   const int F = a.L.F, H = a.L.H;
@@ -774,9 +776,9 @@ __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_fwd(AttnArgs a) {
 }
 
 // ============================================================ aggregation bwd
-template <typename T, int VE, int P, int LPH_CT>
+template <typename T, int VE, int P, int LPH_CT, bool SHORT>
 __global__ void __launch_bounds__(ATT_MAX_BLOCK) k_agg_bwd(AttnArgs a) {
-  constexpr int CH = LPH_CT > 0 ? ATT_CH_FWD : ATT_CH_BWD;
+  constexpr int CH = SHORT ? ATT_CH_BWD : ATT_CH_FWD;
   LaneMap<P> m;
   if (!lane_setup<VE, P, LPH_CT>(a, m)) return;
   const int F = a.L.F, H = a.L.H;

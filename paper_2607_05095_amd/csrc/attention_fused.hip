@@ -135,15 +135,18 @@ fast_status_t attn_run(const char* fn, Op op, const fast_tcsr_t* g, int H, int d
                 (long long)a.ldkv, a.L.F);
   // fp32 rows whose heads break the 16-byte alignment (dh % 4 != 0) but whose
   // width does not (F % 4 == 0): row-major lanes, so every row moves as
-  // 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).  The separate
-  // operators only where a row fills more than half of the least 16 lanes: the
-  // four of them on 66,000 ragged segments of 2 x 6 / 2 x 10 / 2 x 14 / 2 x 18, us,
-  // head-major 44 / 69 / 71 / 110, row-major 74 / 78 / 82 / 85.
+  // 16-byte accesses (FAST_ATTN_ROWMAJOR=0 turns it off).  They take 16 lanes or
+  // more per row, so the separate operators have them where a row fills more
+  // than half of 16, and wider rows, whose lanes can stand idle too, where
+  // segments are not mostly short.  Head-major / row-major, us: ragged segments
+  // of 2.4 edges, 2 x 6 39 / 74, 2 x 14 58 / 82, 2 x 18 94 / 85, 2 x 50 140 / 152,
+  // 2 x 66 224 / 258; of 10 edges, 2 x 18 180 / 137, 2 x 50 359 / 308, 2 x 66 507 / 434.
   const bool fused_op = op == Op::kAttnFwd || op == Op::kAttnBwd || op == Op::kAttnFwdIdx ||
                         op == Op::kAttnBwdIdx;
   a.L.rm = false;
   if (rowmajor_enabled() && dt == FAST_F32 && H == 2 && dh % 4 != 0 &&
-      (H * dh) % 4 == 0 && (H * dh) / 4 <= 64 && (fused_op || (H * dh) / 4 > 8)) {
+      (H * dh) % 4 == 0 && (H * dh) / 4 <= 64 &&
+      (fused_op || ((H * dh) / 4 > 8 && ((H * dh) / 4 <= 16 || g->num_edges >= 4 * g->num_dst)))) {
     bool al = true;
     for (int k = 0; k < nrows; ++k)
       if (rows[k] && !aligned(rows[k], 16)) al = false;

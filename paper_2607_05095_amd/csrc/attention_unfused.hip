@@ -8,13 +8,13 @@
 
 namespace fast {
 
-template <typename T, int VE, int P, int LPH>
+template <typename T, int VE, int P, int LPH, bool SHORT>
 static void launch_unfused(Op op, const AttnArgs& a, dim3 grid, dim3 block, hipStream_t st) {
   switch (op) {
     case Op::kSoftmaxFwd: hipLaunchKernelGGL((k_softmax_fwd<T, VE, P, LPH>), grid, block, 0, st, a); break;
-    case Op::kSoftmaxBwd: hipLaunchKernelGGL((k_softmax_bwd<T, VE, P, LPH>), grid, block, 0, st, a); break;
+    case Op::kSoftmaxBwd: hipLaunchKernelGGL((k_softmax_bwd<T, VE, P, LPH, SHORT>), grid, block, 0, st, a); break;
     case Op::kAggFwd: hipLaunchKernelGGL((k_agg_fwd<T, VE, P, LPH>), grid, block, 0, st, a); break;
-    case Op::kAggBwd: hipLaunchKernelGGL((k_agg_bwd<T, VE, P, LPH>), grid, block, 0, st, a); break;
+    case Op::kAggBwd: hipLaunchKernelGGL((k_agg_bwd<T, VE, P, LPH, SHORT>), grid, block, 0, st, a); break;
     default: break;
   }
 }
@@ -44,10 +44,12 @@ bool attn_launch_unfused(Op op, fast_dtype_t dt, const AttnArgs& a, dim3 grid, d
   }
   const bool bf = dt == FAST_BF16;
   const int VE = a.L.VE, P = a.L.P, LPH = a.L.LPH;
+  const bool mostly_short = a.E < 8 * a.N;   // fewer edges than a chunk of ten (k_softmax_bwd)
 #define FAST_TRY(T_, VE_, P_, L_)                                                     \
   if (bf == std::is_same<T_, uint16_t>::value && VE == VE_ && P == P_ &&              \
       (L_ == 0 || LPH == L_)) {                                                       \
-    launch_unfused<T_, VE_, P_, L_>(op, a, grid, block, st);                          \
+    if (L_ == 0 && mostly_short) launch_unfused<T_, VE_, P_, L_, L_ == 0>(op, a, grid, block, st); \
+    else launch_unfused<T_, VE_, P_, L_, false>(op, a, grid, block, st);              \
     return true;                                                                      \
   }
   FAST_ATTN_FAST_SET(FAST_TRY)
