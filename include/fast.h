@@ -117,7 +117,7 @@ fast_status_t fast_csr_offsets(const int32_t* counts, int64_t n, int32_t* offset
                                void* ws, size_t ws_bytes, fast_stream_t stream);
 
 /* The offsets of several blocks (the layer blocks of one sampled batch, Sec. 5)
- * in one pair of launches: for b < nblocks, offsets[b] receives the offsets of
+ * in one or two launches: for b < nblocks, offsets[b] receives the offsets of
  * counts[b] ([n[b]]), exactly as fast_csr_offsets would.  counts, n and
  * offsets are HOST arrays of nblocks device pointers / sizes.  Up to 8 blocks
  * of at most 2048 * 2048 counts each share the launches; otherwise the blocks
@@ -240,12 +240,16 @@ fast_status_t fast_sample_recent(const fast_temporal_graph_t* g, const int64_t* 
  * row saves once each batch is compressed).  freq is ACCUMULATED into, so
  * batches may be counted over several calls; the caller zeroes it first.
  * ids: device int64; batch_offsets: HOST int64 [num_batches+1],
- * non-decreasing; freq: device int32 [id_bound].  A few launches per batch.
+ * non-decreasing; freq: device int32 [id_bound].  Dense universes (id_bound
+ * at most 32 times the mean batch size) and those that cannot be staged take a
+ * few launches per batch, other sparse ones of up to 2^28 ids two per group of
+ * up to 8 batches.
  * Limits: id_bound < 2^32, num_batches < 2^31 - 1.
  * Workspace: fast_access_count_workspace(id_bound) bytes, 16-byte aligned
- *   (a byte of batch bits per id for up to 32 batches, else a batch stamp
- *   per id; for dense universes, id_bound at most 32 times the mean batch
- *   size, the same space holds up to four byte maps, one per batch).
+ *   (up to four byte maps of a dense universe, one per batch; the staged ids
+ *   of a group of batches of a sparse one; where not even the largest batch
+ *   fits, or beyond 2^28 ids, a byte of batch bits per id for up to 32 batches,
+ *   else a batch stamp per id).
  * ------------------------------------------------------------------------ */
 size_t fast_access_count_workspace(int64_t id_bound);
 fast_status_t fast_access_count(const int64_t* ids, const int64_t* batch_offsets,
@@ -324,8 +328,11 @@ fast_status_t fast_time_encode_batched(int nblocks, const fast_tcsr_t* const* g,
  * summed over every edge of the block.  The sine of the fp32 argument, the
  * products and the sums are fp64 (results rounded once to fp32), so a column
  * whose terms nearly cancel keeps its accuracy.  Deterministic: the order of
- * the sums depends only on N and d_t, and repeated calls give bitwise-equal
- * results.  domega, dphi: [d_t] fp32 device, overwritten (zeros when E = 0).
+ * the sums depends only on N, E, the first and last offset, d_t and dte's type
+ * and alignment (which set the width of its accesses), and repeated calls give
+ * bitwise-equal results.  The work is shared out over min(N / 8, 1280)
+ * workgroups at most, so a block of very few destinations is slow.
+ * domega, dphi: [d_t] fp32 device, overwritten (zeros when E = 0).
  * Reads g->dst_offsets, g->dst_t, g->edge_t.  dte: [E, d_t] of dte_dtype.
  * Limits: 1 <= d_t, and d_t / v <= 256 for the widest v in {8 (bf16 only),
  * 4, 2, 1} that divides d_t and matches dte's alignment (so d_t <= 256

@@ -28,7 +28,11 @@
 //     fp32 4 x 32 (3.6 edges on average) 89 / 61 / 61, forward and backward
 //     of ragged fp32 2 x 50 321 / 408 / 308, of ragged bf16 2 x 50 148 / 191 /
 //     136; full chunks the same with all but the mask (fp32 2 x 50, 2.64 M
-//     edges: 1161 / 1185 / 1157).
+//     edges: 1161 / 1185 / 1162).  Indexed rows, whose index loads the branches
+//     hold up, have a path of their own for full chunks.  Segments of hundreds
+//     of edges pay 2-10 % for the branches (500 of 1000 edges, fp32 2 x 64
+//     forward 218 -> 237).  The backward's second reading of long segments
+//     (past the edges whose scalars stay in registers) re-reads the last row.
 //   * Every destination row is produced by exactly one sub-wavefront: the
 //     results are deterministic run to run (unlike the paper's edge-parallel
 //     atomicAdd aggregation, which is prior art for a different GPU).
@@ -565,8 +569,8 @@ __device__ __forceinline__ void load_rows(const T* __restrict__ rows, int64_t ba
 // lives in lane i % LPH of the head, slot i / LPH (0 past the segment's end),
 // so that a chunk moves as one or a few accesses (with K's single reading,
 // 66,000 segments of 20 edges, bf16 4 x 32: the four operators 610 -> 442 us);
-// get passes an entry to all lanes.  LPH = 0 (lanes per head known at run time only): every lane holds
-// all entries.
+// get passes an entry to all lanes.  LPH = 0 (lanes per head known at run time
+// only): every lane holds all entries.
 template <int LPH, int CH>
 struct LaneScalars {
   static constexpr int L = LPH > 0 ? LPH : 1;

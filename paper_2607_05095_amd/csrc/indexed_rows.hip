@@ -420,7 +420,7 @@ static uint32_t grid_cap(int64_t n, int64_t per, uint32_t cap = 8192) {
 constexpr int IA_THREADS = 256;
 constexpr int IA_PIECE = 64;   // occurrences summed by one group
 constexpr int IA_ROWS = 4;   // rows per group of lanes on large outputs
-constexpr int64_t IA_GROUPS_FILL = 16384;   // groups that fill the chip twice
+constexpr int64_t IA_GROUPS_FILL = 16384;   // groups that fill the chip twice at 64 lanes, half of it at 16
 constexpr int IA_PART_UNROLL = 4;   // partial sums in flight per lane of a long row
 
 constexpr int IA_GROUP_MIN = 16;   // fewest pieces per group of the second level
@@ -493,14 +493,6 @@ __device__ __forceinline__ void ia_sum_partials(const double* __restrict__ part,
 #pragma unroll
     for (int t = 0; t < VE; ++t) acc[t] += part[m * D + c * VE + t];
 }
-
-// Eight fp32 values of a row sum (the bf16 sources' widest vector).
-template <> struct VecIO<float, 8> {
-  __device__ static void store(float* p, const float* x) {
-    VecIO<float, 4>::store(p, x);
-    VecIO<float, 4>::store(p + 4, x + 4);
-  }
-};
 
 // Row sources of the index-add kernels.  Position p = occ[j] contributes, to
 // chunk c (VE values) of its row's sum:
@@ -765,10 +757,10 @@ __device__ __forceinline__ void ia_long_row(
 
 // R consecutive rows by one group of lanes: zeros for a row without
 // occurrences, a long row added from the level below.  The rows' occurrences
-// lie side by side in occ, so with R > 1 the group walks them as one stream: the lanes look up as many positions at
-// once as there are lanes, ROW_UNROLL source rows are in flight whichever
-// output rows they belong to, and a row's sum is stored where its last
-// position has been added.  A row of one or two positions by itself waits
+// lie side by side in occ, so with R > 1 the group walks them as one stream:
+// the lanes look up as many positions at once as there are lanes, ROW_UNROLL
+// source rows are in flight whichever output rows they belong to, and a row's
+// sum is stored where its last position has been added.  A row of one or two positions by itself waits
 // for offset, position, segment and row one after the other: with 1 / 2 / 4 /
 // 8 rows per group the fp32 sums of 0.44 M and 0.58 M rows (half of 2.64 M
 // positions in hub rows) took 174 / 141 / 125 / 131 and 218 / 169 / 146 / 151

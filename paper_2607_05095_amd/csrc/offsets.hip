@@ -52,8 +52,8 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_off_batch_reduce(OffBatch B, u
 }
 
 // Blocks of few tiles: a tile adds up the counts before it itself, and the
-// reduce launch is saved.  At most OFF_ONE_TILES tiles per block: 6 x 2048
-// counts are 48 loads per thread, in flight together.
+// reduce launch is saved.  At most OFF_ONE_TILES tiles per block: up to 6 x 2048
+// counts before a tile are 6 rounds of 8 loads per thread.
 constexpr int64_t OFF_ONE_TILES = 7;
 
 __global__ void __launch_bounds__(SCAN_THREADS) k_off_batch_down(OffBatch B, const uint32_t* tsum) {

@@ -9,16 +9,17 @@
 // of it, in entry order.  Up to SR_TILED roots the calls are bound by
 // latency, not by bytes, and take two launches:
 //   * 16 or 4 lanes search for one root, that many probes at a time: a hub's
-//     4e6 entries take 6 or 10 dependent loads instead of 22;
+//     4e6 entries take 6 or 11 dependent loads instead of 22;
 //   * a workgroup's roots are one scan tile: the search leaves the tile's sum,
 //     and the fill adds up the sums of the tiles before its own, scans its
 //     own counts, writes the offsets and copies its roots' neighbours, times
 //     and edge ids (16 lanes per root; one root's entries are contiguous).
-// 6,000 roots and then their 60,000 places, k = 10, 2e7 events: 40.6 us with a
-// thread per search and a scan of its own (4 launches a hop), 24 now.  More
-// roots are bound by the probes and copies themselves (24,000 roots and their
-// 240,000 places: 16 / 4 / 1 lanes a search 73 / 59 / 56 us): they keep a
-// thread per search and the scan of its own.
+// 6,000 roots and then their 60,000 places, k = 10, 2e7 events, the same roots
+// again and again: 40.6 us with a thread per search and a scan of its own (4
+// launches a hop), 23.5 now; fresh roots in swept caches, hop 1 / hop 2, 24.8 /
+// 30.2 and 12.9 / 22.2.  More roots are bound by the probes and copies
+// themselves (24,000 roots and their 240,000 places: 16 / 4 / 1 lanes a search
+// 73 / 59 / 56 us): they keep a thread per search and the scan of its own.
 // The output is a function of the inputs alone.
 #include "scan.h"
 
@@ -33,7 +34,9 @@ constexpr int SR_SMALL = 16, SR_LARGE = 64;
 constexpr int64_t SR_MAX_TILES = 2048;
 constexpr int64_t SR_TILED = SR_MAX_TILES * SR_LARGE;
 // 16 lanes per search while they are too few to be bound by their probes
-// (6,000 roots: 5.0 us against 6.5 with 4 lanes; 60,000: 12.9 against 7.8).
+// (6,000 roots: 5.0 us against 6.5 with 4 lanes; 60,000: 12.9 against 7.8; the
+// call on fresh roots, 16 / 4 lanes: 600 of them 11.6 / 13.7 us, 6,000 12.9 / 14.8,
+// 12,000 14.2 / 15.8, 18,000 15.6 / 16.7, 36,000 18.6 / 18.6).
 constexpr int64_t SR_WIDE_SEARCH = 8192;
 
 // First p in [a, b) with !(ts[p] < t), b if none; every lane of the group of

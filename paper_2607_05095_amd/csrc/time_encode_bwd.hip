@@ -20,17 +20,19 @@
 // fmaf(max|omega|, |dt|, max|phi|) exceeds 1e6 (or is not finite) is left
 // to the library sine in a cold second pass of the workgroups that met one.
 //
-// Determinism: the reduction order depends only on N, E, d_t and
-// the width of a thread's accesses.
-// Workgroup b of nblk = tb_grid(N, E, VEC) owns the b-th of nblk equal ranges of
-// edges; each thread accumulates its column chunk over its rows in a fixed
+// Determinism: the reduction order depends only on N, E, the first and last
+// offset, d_t and the width of a thread's accesses.  Workgroup b of
+// nblk = tb_grid(N, E, VEC) owns the b-th of nblk equal ranges of edges; each thread accumulates its column chunk over its rows in a fixed
 // order, the row lanes are added in lane order through LDS, and a second
 // kernel adds the per-workgroup partials in a fixed tree.  Repeated calls give
 // bitwise-identical results.
 //
-// Bound by fp64 issue (about 20 vector instructions per element), so the chip
-// has to stay full to the end: as many workgroups as are resident at once, all
-// with the same number of edges.  Groups of 32 segments dealt out to 2048
+// About 23 vector instructions per element, most of them fp64: 153 us of issue
+// for 2.64 M edges x 100, against 170 of their bytes.  Neither is reached: the
+// vector units are busy in 56 % of the kernel's cycles, and the five waves of a
+// SIMD wait in 73 % of theirs, for rows of dte and at the three barriers of a
+// tile.  So the chip has to stay full to the end: as many workgroups as are
+// resident at once where N allows them, all with the same number of edges.  Groups of 32 segments dealt out to 2048
 // workgroups left some with five groups and most with four, in two rounds of
 // residence: 2.64 M edges of 264,000 segments x 100 fp32 286 -> 258 us, 0.19 M of
 // ragged ones x 128 bf16 52 -> 41 us.  More rows of dte in flight per thread
@@ -40,7 +42,7 @@
 namespace fast {
 
 constexpr int TB_THREADS = 256;
-constexpr int TB_SEGS = 8;           // destination segments per workgroup, on average, up to
+constexpr int TB_SEGS = 8;           // fewest destination segments per workgroup, on average
 constexpr int TB_MAX_BLOCKS = 1280;  // 5 workgroups per CU, what the registers hold at once
 constexpr int TB_WIN = TB_THREADS;   // segments whose ends and times a tile stages
 constexpr int TB_TILE_MAX = 256;     // rows staged per tile
@@ -55,7 +57,8 @@ __host__ __device__ inline int64_t tb_blocks(int64_t N) {
 // (20,000 edges 12 us with 156 workgroups, 18 with 62), 192 beyond or 320 where a
 // thread has 8 columns and twice the sums (0.24 M edges x 100 fp32: 32 us so, 33.5
 // with 320 edges; x 128 bf16: 39 us so, 46 with 192), up to the workgroups
-// resident at once (8 columns per thread: 4 per CU).
+// resident at once (8 columns per thread: 4 per CU) and up to tb_blocks(N), for
+// which the workspace has room: 1e5 edges of 8 segments are left to one (4.5 ms).
 inline int64_t tb_grid(int64_t N, int64_t E, int vec) {
   const int64_t most = tb_blocks(N), cap = vec >= 8 ? 1024 : TB_MAX_BLOCKS;
   const int64_t few = (E + 127) / 128 < 512 ? (E + 127) / 128 : 512, many = E / (vec >= 8 ? 320 : 192);
